@@ -239,11 +239,13 @@ lce_status lce_bconv2d_mfma_weights(const lce_bconv2d_desc *desc, const int32_t 
  * lce_bconv2d (multiplier/bias for FLOAT32, thresholds and optional flip for
  * BITPACKED), with the widened filters in place of w_packed and either
  * pad_value (no correction table).
- * The work is split by shape between three schedules: filter-stationary
+ * The work is split by shape between four schedules: filter-stationary
  * (each wave keeps its filters in registers and runs through about one
  * CU's share of pixel blocks; by default up to 36 K steps of 64
  * channels, up to 72 when an instance is forced), K-split
- * (the waves of a workgroup divide K; long K) and pixel-split (the rest).
+ * (the waves of a workgroup divide K; long K), pixel-split (the rest), and
+ * streaming (tiles of pixels x filters with the filters read from the packed
+ * copy step by step, any K; where many tiles make it the faster one).
  * lce_set_tuning can force a schedule, an instance or a tile for tests and
  * tuning; every choice gives the identical output.
  * w_fp4 must be the output of lce_bconv2d_mfma_weights for a descriptor with
@@ -280,7 +282,8 @@ lce_status lce_bconv2d_mfma(const lce_bconv2d_desc *desc, const int32_t *x_packe
  * filters over few channels) return LCE_EUNSUPPORTED before anything is
  * launched, and the caller runs lce_bitpack and lce_bconv2d_mfma instead.
  * LCE_TUNE_MFMA_SCHEDULE 1 or 2 restricts the choice to that schedule (2
- * then takes any K); 3, the pixel split, has no fused form and is refused.
+ * then takes any K); 3 and 4, the pixel split and the streaming schedule,
+ * have no fused form and are refused.
  * Errors: as lce_bconv2d_mfma, plus LCE_EUNSUPPORTED (above) and LCE_EALIGN
  *         for an x that is not 16-byte aligned. */
 lce_status lce_quantize_bconv2d_mfma(const lce_bconv2d_desc *desc, const float *x,
@@ -341,14 +344,18 @@ typedef enum {
     LCE_TUNE_XOR_KS = 1,          /* lce_bconv2d: waves sharing a block's K range 1/2/4 */
     LCE_TUNE_MFMA_SCHEDULE = 2,   /* lce_bconv2d_mfma and lce_quantize_bconv2d_mfma:
                                      1 filter-stationary (where an instance fits),
-                                     2 K split, 3 pixel split (not fused)               */
+                                     2 K split, 3 pixel split (not fused), 4 streaming
+                                     (where a tile fits; not fused)                     */
     LCE_TUNE_MFMA_FS_KS = 3,      /* filter-stationary instance: K steps per wave       */
     LCE_TUNE_MFMA_FS_S = 4,       /* filter-stationary instance: waves per filter block */
-    LCE_TUNE_MFMA_FS_WPC = 5,     /* filter-stationary grid: 1 or 2 workgroups per CU   */
+    LCE_TUNE_MFMA_FS_WPC = 5,     /* filter-stationary and streaming grids: 1 or 2 workgroups
+                                     per CU                                             */
     LCE_TUNE_MFMA_FS_PAD = 6,     /* -1: no LDS claim that spreads workgroups over CUs  */
     LCE_TUNE_MFMA_PACKED = 7,     /* -1: load widened filters where packed ones would do */
-    LCE_TUNE_MFMA_TILE_M = 8,     /* K-split / pixel-split tile: 32-pixel blocks        */
-    LCE_TUNE_MFMA_TILE_N = 9,     /* K-split / pixel-split tile: 32-filter blocks       */
+    LCE_TUNE_MFMA_TILE_M = 8,     /* K-split / pixel-split tile: 32-pixel blocks;
+                                     streaming: 32-pixel blocks per wave, 2 or 4        */
+    LCE_TUNE_MFMA_TILE_N = 9,     /* K-split / pixel-split / streaming tile: 32-filter
+                                     blocks                                             */
     LCE_TUNE_MFMA_FS_WINDOW = 10, /* -1: filter-stationary workgroups stage whole padded
                                      rows, also where a share's window of columns would do */
     LCE_TUNE_COUNT = 11

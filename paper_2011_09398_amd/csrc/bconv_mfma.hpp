@@ -60,7 +60,8 @@ constexpr uint32_t kFp4SignBits = 0x88888888u;
 // K steps (S*KS) a filter-stationary instance covers at most.
 constexpr int kFsMaxSteps = 72;
 
-struct MfmaParams {
+// What every matrix-core kernel reads: tensors, geometry, divisors.
+struct MfmaGeom {
     const uint32_t *x;      // [N][H][W][Cw] bitpacked activations
     const u32x4 *wexp;      // [KH*KW*CwE][CoutP] widened filters (16 bytes = 32 values)
     const uint32_t *wpk;    // [KH*KW*CwE][CoutP] the same filters packed (4 bytes = 32 values)
@@ -85,6 +86,9 @@ struct MfmaParams {
     FastDiv div_cwh, div_kw;         // cwe / 2 (word pairs per tap), kw
     FastDiv div_groups;              // region_vec-word groups per location
     FastDiv div_ks_gx;               // K-split schedule: pixel tiles (grid x)
+};
+
+struct MfmaParams : MfmaGeom {
     // filter-stationary schedules: A-tile offset (in 16-byte words) of K step
     // s = (tap t = ky*KW + kx, word pair q) from a pixel's window origin,
     // 2q*plane + ky*PW + kx (plane = tile_rows*pw), in bits 0-23, and the
@@ -140,8 +144,9 @@ __device__ __forceinline__ u32x4 widen_valid_mask(uint32_t valid) {
 __device__ __forceinline__ mfma_v16f mfma_fp4(u32x4 a, u32x4 b, mfma_v16f c) {
     const mfma_v8i av = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
     const mfma_v8i bv = {(int)b.x, (int)b.y, (int)b.z, (int)b.w, 0, 0, 0, 0};
-    // operand formats 4 = e2m1; scales 127 = 2^0
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 4, 4, 0, 127, 0, 127);
+    // operand formats 4 = e2m1; constant-zero scale operands select the form
+    // without scales
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 4, 4, 0, 0, 0, 0);
 }
 
 // Threshold as a bound on the unclamped dot, as a float: bit = clamp(dot) <
@@ -208,7 +213,7 @@ __device__ __forceinline__ uint32_t block_bits(const mfma_v16f &val, float T, ui
 // kernel: the compiler would otherwise load the fields in several dependent
 // batches (behind branches), each first touch of a line a full memory
 // latency.
-__device__ __forceinline__ void fetch_arg_lines(const MfmaParams &p) {
+__device__ __forceinline__ void fetch_arg_lines(const MfmaGeom &p) {
     asm volatile("" ::"s"(p.x), "s"(p.oh), "s"(p.m), "s"(p.div_pw.d), "s"(p.div_ks_gx.d));
 }
 
@@ -222,7 +227,7 @@ __device__ __forceinline__ uint64_t block_flip(const uint32_t *flip, int word_in
 }
 
 // Stacked padded row of output pixel m's window origin, and its column.
-__device__ __forceinline__ void mfma_pixel(const MfmaParams &p, int m, int &row, int &col) {
+__device__ __forceinline__ void mfma_pixel(const MfmaGeom &p, int m, int &row, int &col) {
     const uint32_t img = fast_div((uint32_t)m, p.div_ohw);
     const uint32_t r = (uint32_t)m - img * p.div_ohw.d;
     const uint32_t oy = fast_div(r, p.div_ow);
@@ -547,7 +552,7 @@ __global__ __launch_bounds__(kMfmaThreads) void bconv2d_mfma_kernel(MfmaParams p
 // tile_rows x pw locations from padded row row0 and padded column c0 (c0 = 0
 // unless a filter-stationary workgroup stages only its share's window of
 // columns, pw then being the window's width).
-__device__ __forceinline__ bool region_inside(const MfmaParams &p, int row0, int c0, int rc) {
+__device__ __forceinline__ bool region_inside(const MfmaGeom &p, int row0, int c0, int rc) {
     const int r = (int)fast_div((uint32_t)rc, p.div_pw);
     const int c = c0 + rc - r * p.pw;
     const int R = row0 + r;
@@ -562,8 +567,8 @@ __device__ __forceinline__ bool region_inside(const MfmaParams &p, int row0, int
 // instead of reloading it from the kernel arguments wherever it is used (it
 // treats argument loads as free to repeat, and each repeat is a dependent
 // scalar-cache round trip in the set-up).
-__device__ __forceinline__ MfmaParams pinned_geometry(const MfmaParams &p) {
-    MfmaParams q = p;
+__device__ __forceinline__ MfmaGeom pinned_geometry(const MfmaGeom &p) {
+    MfmaGeom q = p;
     asm volatile("" : "+s"(q.n), "+s"(q.h), "+s"(q.w), "+s"(q.cw), "+s"(q.cwe), "+s"(q.pw),
                       "+s"(q.ph), "+s"(q.pt), "+s"(q.pl), "+s"(q.sh), "+s"(q.sw), "+s"(q.ow),
                       "+s"(q.region_vec), "+s"(q.pad_zero), "+s"(q.m));
@@ -589,12 +594,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, ui
 }
 
 // the bitpacked input as a buffer
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t input_buffer(const MfmaParams &p) {
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t input_buffer(const MfmaGeom &p) {
     return buffer_of(p.x, (uint32_t)p.n * p.h * p.w * p.cw * 4u);
 }
 
 // the widened (16 bytes per element) or packed (4 bytes) filters as a buffer
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t filter_buffer(const MfmaParams &p, bool packed) {
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t filter_buffer(const MfmaGeom &p, bool packed) {
     const uint32_t elems = (uint32_t)p.kh * p.kw * p.cwe * p.coutp;
     return packed ? buffer_of(p.wpk, elems * 4u) : buffer_of(p.wexp, elems * 16u);
 }
@@ -618,7 +623,7 @@ struct RegionChunk {
 // byte offset in the input of word `word` of region location rc
 // (kBufOutside when the location is outside the image; region origin as in
 // region_inside)
-__device__ __forceinline__ int region_offset(const MfmaParams &p, int row0, int c0, int rc,
+__device__ __forceinline__ int region_offset(const MfmaGeom &p, int row0, int c0, int rc,
                                              int word, bool &inside) {
     const int r = (int)fast_div((uint32_t)rc, p.div_pw);
     const int c = c0 + rc - r * p.pw;
@@ -632,12 +637,12 @@ __device__ __forceinline__ int region_offset(const MfmaParams &p, int row0, int 
 }
 
 // elements of the region: plane * Cw / region_vec
-__device__ __forceinline__ int region_elements(const MfmaParams &p, int plane) {
+__device__ __forceinline__ int region_elements(const MfmaGeom &p, int plane) {
     return p.region_vec == 4 ? plane * (p.cw >> 2) : plane * p.cw;
 }
 
 template <int NT>
-__device__ __forceinline__ void region_load(const MfmaParams &p, int row0, int c0, int plane,
+__device__ __forceinline__ void region_load(const MfmaGeom &p, int row0, int c0, int plane,
                                             int tid, int e0, RegionChunk &ch) {
     const int total = region_elements(p, plane);
     const __amdgpu_buffer_rsrc_t xb = input_buffer(p);
@@ -679,7 +684,7 @@ __device__ __forceinline__ void region_load(const MfmaParams &p, int row0, int c
 // Widen a loaded chunk into the A tile: +1.0/-1.0 from the bits, 0.0 at
 // padding locations under zero padding.
 template <int NT>
-__device__ __forceinline__ void region_widen(const MfmaParams &p, const RegionChunk &ch,
+__device__ __forceinline__ void region_widen(const MfmaGeom &p, const RegionChunk &ch,
                                              u32x4 *atile, int plane, int tid, int e0) {
     const int total = region_elements(p, plane);
 #pragma unroll
@@ -702,7 +707,7 @@ __device__ __forceinline__ void region_widen(const MfmaParams &p, const RegionCh
 // kRegU*NT elements: load, wait, widen), then the words past Cw: +1.0, or
 // 0.0 outside the image under zero padding.
 template <int NT>
-__device__ __forceinline__ void region_finish(const MfmaParams &p, u32x4 *atile, int row0,
+__device__ __forceinline__ void region_finish(const MfmaGeom &p, u32x4 *atile, int row0,
                                               int c0, int plane, int tid) {
     const int total = region_elements(p, plane);
     for (int e0 = kRegU * NT; e0 < total; e0 += kRegU * NT) {
@@ -739,7 +744,7 @@ struct RegionChunkF {
 };
 
 template <int NT>
-__device__ __forceinline__ void region_load_f(const MfmaParams &p, int row0, int c0, int plane,
+__device__ __forceinline__ void region_load_f(const MfmaGeom &p, int row0, int c0, int plane,
                                               int tid, int e0, RegionChunkF &ch) {
     const int total = plane * p.cw;
     const __amdgpu_buffer_rsrc_t xb =
@@ -770,7 +775,7 @@ __device__ __forceinline__ void region_load_f(const MfmaParams &p, int row0, int
 }
 
 template <int NT>
-__device__ __forceinline__ void region_widen_f(const MfmaParams &p, const RegionChunkF &ch,
+__device__ __forceinline__ void region_widen_f(const MfmaGeom &p, const RegionChunkF &ch,
                                                u32x4 *atile, int plane, int tid, int e0) {
     const int total = plane * p.cw;
 #pragma unroll
@@ -793,7 +798,7 @@ __device__ __forceinline__ void region_widen_f(const MfmaParams &p, const Region
 // The rest of the float region after the first chunk, then the words past
 // Cw (as region_finish).
 template <int NT>
-__device__ __forceinline__ void region_finish_f(const MfmaParams &p, u32x4 *atile, int row0,
+__device__ __forceinline__ void region_finish_f(const MfmaGeom &p, u32x4 *atile, int row0,
                                                 int c0, int plane, int tid) {
     const int total = plane * p.cw;
     for (int e0 = kRegUF * NT; e0 < total; e0 += kRegUF * NT) {
@@ -893,7 +898,7 @@ __global__ __launch_bounds__(kMfmaThreads) void bconv2d_mfma_ks_kernel(MfmaParam
     const int TR = p.tile_rows, PW = p.pw, plane = TR * PW;
     u32x4 *atile = smem;                                 // [cwe][TR][PW] e2m1
 
-    const MfmaParams g = pinned_geometry(p);     // (geometry in scalar registers)
+    const MfmaGeom g = pinned_geometry(p);     // (geometry in scalar registers)
     int row0, col0;
     mfma_pixel(g, m0, row0, col0);
     int a_lane[MBW];                                     // this lane's A offset per pixel block
@@ -1209,7 +1214,7 @@ __global__ __launch_bounds__(kMfmaThreads) void bconv2d_mfma_fs_kernel(MfmaParam
     // past the A tile: the exchange buffer (S > 1)
     f32x4 *red = reinterpret_cast<f32x4 *>(smem + p.cwe * plane);
 
-    const MfmaParams g = pinned_geometry(p);     // (geometry in scalar registers)
+    const MfmaGeom g = pinned_geometry(p);     // (geometry in scalar registers)
     int row0, col0;
     mfma_pixel(g, m0, row0, col0);
     // the region's first padded column

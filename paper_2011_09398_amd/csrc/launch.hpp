@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include "bconv_mfma.hpp"
+#include "bconv_mfma_stream.hpp"
 
 namespace lce {
 
@@ -27,6 +28,10 @@ void launch_mfma_fs(const MfmaParams &p, int ks, int s, bool pk, bool qf, int ou
 // (p.pw = the window's width; every share within one output row)
 void launch_mfma_fs_window(const MfmaParams &p, int ks, int s, bool pk, bool qf, int out_type,
                            dim3 grid, size_t lds, hipStream_t stream);
+
+// streaming schedule: MB x NB blocks per wave
+void launch_mfma_stream(const StreamParams &p, int out_type, int mb, int nb, dim3 grid,
+                        size_t lds, hipStream_t stream);
 
 // quantize-fused XOR/POPCOUNT convolution (float input, Cw = C_in/32 words
 // per pixel): whether an instance exists, and its launch

@@ -491,20 +491,33 @@ int64_t mfma_weight_bytes(const lce_bconv2d_desc &d) {
 
 int device_max_lds() { return device_attribute<hipDeviceAttributeMaxSharedMemoryPerBlock>(65536); }
 
+// Padded rows that `rows` consecutive output rows read at most, wherever they
+// start: (rows - 1) strides and a window, and the rows by which stacked padded
+// images are further apart than their output rows, once per image boundary
+// that `rows` rows can cross (`aligned`: they start at a multiple of `rows`).
+int64_t padded_rows(const lce::MfmaGeom &p, int64_t rows, bool aligned) {
+    int64_t cross = rows > 1 ? (rows - 2) / p.oh + 1 : 0;
+    if (aligned && p.oh % rows == 0) cross = 0;
+    if (aligned && rows % p.oh == 0) cross = rows / p.oh - 1;
+    const int64_t gap = std::max<int64_t>(0, (int64_t)p.ph - (int64_t)p.oh * p.sh);
+    return (rows - 1) * p.sh + p.kh + cross * gap;
+}
+
 // Stacked padded rows a workgroup of `bm` pixels reads, maximized over the
-// workgroups (the span repeats with the image, so one period suffices).
-int mfma_tile_rows(const lce::MfmaParams &p, int bm) {
+// workgroups (the span repeats with the image, so one period suffices, and
+// the search ends where it meets the bound of bm pixels anywhere, as it
+// mostly does within a few workgroups).
+int mfma_tile_rows(const lce::MfmaGeom &p, int bm) {
     const int64_t per_img = (int64_t)p.oh * p.ow;
     const int64_t blocks = ((int64_t)p.m + bm - 1) / bm;
-    int64_t g = per_img, b = bm;
-    while (b) { const int64_t t = g % b; g = b; b = t; }
-    const int64_t period = per_img / g;           // blocks until the pattern repeats
+    const int64_t period = per_img / std::gcd<int64_t>(per_img, bm);   // blocks until it repeats
+    const int64_t bound = padded_rows(p, bm % p.ow ? (bm - 2 + p.ow) / p.ow + 1 : bm / p.ow, false);
     auto row_of = [&](int64_t m) {
         const int64_t img = m / per_img, r = m % per_img;
         return img * p.ph + (r / p.ow) * p.sh;
     };
     int64_t best = 0;
-    for (int64_t i = 0; i < std::min(blocks, period + 1); ++i) {
+    for (int64_t i = 0; i < std::min(blocks, period + 1) && best < bound; ++i) {
         const int64_t first = i * bm;
         const int64_t last = std::min(first + bm - 1, (int64_t)p.m - 1);
         best = std::max(best, row_of(last) - row_of(first) + p.kh);
@@ -739,12 +752,10 @@ lce_status mfma_params(const lce_bconv2d_desc &d, const Geometry &g, const void 
     return ok();
 }
 
-// Plans the filter-stationary schedule of a layer and launches it (qf: the
-// input is float32, binarized while staged); false, with nothing launched,
-// when no instance fits.
-bool launch_fs_plan(lce::MfmaParams &p, const lce_bconv2d_desc &d, int64_t cus, int blocks32,
-                    int64_t ksteps, bool qf, hipStream_t stream) {
-    const FsPlan fp = plan_mfma_fs(p, cus, blocks32, (int)ksteps);
+// Launches the filter-stationary plan `fp` (qf: the input is float32,
+// binarized while staged); false, with nothing launched, when no instance fits.
+bool launch_fs_plan(lce::MfmaParams &p, const lce_bconv2d_desc &d, const FsPlan &fp, int64_t cus,
+                    int blocks32, int64_t ksteps, bool qf, hipStream_t stream) {
     if (!fp.shape.ks) return false;
     p.tile_rows = fp.tile_rows;
     p.fs_pixels = fp.pixels;
@@ -782,6 +793,7 @@ bool launch_fs_plan(lce::MfmaParams &p, const lce_bconv2d_desc &d, int64_t cus, 
 struct KsPlan {
     int mbw = 0, nblk = 0, tile_rows = 0;
     int64_t wgs = 0;
+    size_t lds = 0;
 };
 
 KsPlan plan_mfma_ks(const lce::MfmaParams &p, int64_t cus, int blocks32) {
@@ -795,11 +807,12 @@ KsPlan plan_mfma_ks(const lce::MfmaParams &p, int64_t cus, int blocks32) {
         if (env_mb && o[0] != env_mb) continue;
         if (env_nb && o[1] != env_nb) continue;
         const int tr = mfma_tile_rows(p, 32 * o[0]);
-        if (mfma_ks_lds(p, o[0], o[1], tr) > (size_t)device_max_lds()) continue;
+        const size_t lds = mfma_ks_lds(p, o[0], o[1], tr);
+        if (lds > (size_t)device_max_lds()) continue;
         const int64_t wgs = ((int64_t)p.m + 32 * o[0] - 1) / (32 * o[0]) *
                             ((blocks32 + o[1] - 1) / o[1]);
-        if (2 * wgs >= 3 * cus) return KsPlan{o[0], o[1], tr, wgs};
-        if (wgs > best.wgs) best = KsPlan{o[0], o[1], tr, wgs};
+        if (2 * wgs >= 3 * cus) return KsPlan{o[0], o[1], tr, wgs, lds};
+        if (wgs > best.wgs) best = KsPlan{o[0], o[1], tr, wgs, lds};
     }
     return best;
 }
@@ -811,12 +824,230 @@ bool launch_ks_plan(lce::MfmaParams &p, const lce_bconv2d_desc &d, const KsPlan 
     if (!kp.mbw) return false;
     p.tile_rows = kp.tile_rows;
     p.div_plane = lce::make_fastdiv((uint32_t)(kp.tile_rows * p.pw));
-    const size_t lds = mfma_ks_lds(p, kp.mbw, kp.nblk, kp.tile_rows);
     const dim3 grid((unsigned)(((int64_t)p.m + 32 * kp.mbw - 1) / (32 * kp.mbw)),
                     (unsigned)((blocks32 + kp.nblk - 1) / kp.nblk));
     p.div_ks_gx = lce::make_fastdiv(grid.x);
-    lce::launch_mfma_ksplit(p, d.out_type, kp.nblk, kp.mbw, qf, grid, lds, stream);
+    lce::launch_mfma_ksplit(p, d.out_type, kp.nblk, kp.mbw, qf, grid, kp.lds, stream);
     return true;
+}
+
+// The plan of the streaming schedule: blocks per wave (mb x nb), waves side by
+// side over filters (wf), the tile of output rows and columns, and its price.
+struct StreamPlan {
+    int mb = 0, nb = 0, wf = 0;
+    int th = 0, tw = 0, col_tiles = 0;
+    int tile_rows = 0, width = 0, plane = 0;
+    int64_t tiles = 0;
+    int groups = 0, per_cu = 0;
+    size_t lds = 0;
+    double cost = 0;
+};
+
+// Cycles of a filter-stationary plan: a set-up, then its pixel blocks at 50
+// cycles a product, plus the exchange where waves share a filter block
+// (28x28x128 batch 64: 11.8K predicted, 10.6K measured; batch 256: 28K, 26K;
+// 14x14x256 batch 64: 14K, 13K; 56x56x64->128/s2 batch 64: 9.1K, 8.6K;
+// 56x56x64->64 batch 64: 19.7K, 23K).
+double fs_cycles(const FsPlan &fp) {
+    const int nb = (fp.pixels + 31) / 32;
+    return 5000.0 + (double)nb * fp.wpc * (50.0 * fp.shape.ks + (fp.shape.s > 1 ? 320.0 : 0.0));
+}
+
+// The streaming plan of least price, in cycles of the busiest CU: its first
+// workgroup takes a set-up and its products at 1.35 times the pipe's 32
+// cycles (nothing else to run meanwhile); each further one on the same CU its
+// products at the full rate, and the staging and output that do not overlap
+// them (at 2.1 GHz, measured less the launch: 56x56x64->64 batch 256, tiles of
+// two blocks per wave: 45K, predicted 41K; 28x28x128 batch 256: 30K, 36K;
+// 14x14x256 batch 64: 11K, 10.9K; 7x7x512 batch 256: 31K, 30K; 1x1
+// 28x28x256->512 batch 256: 55K, 67K).  mb == 0: no tile fits the LDS.
+StreamPlan plan_stream(const lce::MfmaGeom &p, int64_t cus, int64_t ksteps, int blocks32) {
+    StreamPlan best;
+    const int force_mb = tuning(LCE_TUNE_MFMA_TILE_M), force_bn = tuning(LCE_TUNE_MFMA_TILE_N);
+    // {mb, nb, wf}
+    static const int kTiles[][3] = {{2, 2, 1}, {2, 2, 2}, {2, 2, 4}, {4, 2, 1}, {4, 2, 2},
+                                    {4, 2, 4}, {4, 1, 1}};
+    const int64_t out_rows = (int64_t)p.n * p.oh;
+    for (const auto &o : kTiles) {
+        StreamPlan s;
+        s.mb = o[0]; s.nb = o[1]; s.wf = o[2];
+        const int bn = s.nb * s.wf, bm = 32 * s.mb * (4 / s.wf);
+        if (force_mb && s.mb != force_mb) continue;
+        if (force_bn && bn != force_bn) continue;
+        if (!force_bn && (s.nb == 1) != (blocks32 == 1)) continue;
+        if (!force_bn && bn > 2 && bn >= 2 * blocks32) continue;
+        s.groups = (blocks32 + bn - 1) / bn;
+        // whole output rows, or tiles of a multiple of 32 columns (so that a
+        // block's 32 pixels stay consecutive) where those fill the tile better
+        double fill = 0;
+        auto consider = [&](int tw) {
+            const int ct = (p.ow + tw - 1) / tw;
+            const int th = (int)std::min<int64_t>(bm / tw, out_rows);
+            const double f = (double)th * p.ow / ((double)bm * ct);
+            if (f <= fill * 1.0625) return;
+            fill = f;
+            s.tw = tw;
+            s.th = th;
+            s.col_tiles = ct;
+        };
+        if (p.ow <= bm) consider(p.ow);
+        for (int tw = bm; tw >= 32; tw /= 2)
+            if (p.ow > tw) consider(tw);
+        s.tile_rows = (int)std::min<int64_t>(padded_rows(p, s.th, true), INT32_MAX / 2);
+        s.width = (s.tw - 1) * p.sw + p.kw;
+        s.tiles = (out_rows + s.th - 1) / s.th * s.col_tiles;
+        const int64_t plane = (int64_t)s.tile_rows * s.width | 1;
+        const int64_t lds = (int64_t)p.cwe * plane * 16 + (32 * bn + ksteps + 4) * 4;
+        // (a pixel's place in the region is kept in 16 bits)
+        if (lds > device_max_lds() || plane * 2 > 65535 || s.tiles * s.groups > INT32_MAX / 2)
+            continue;
+        s.plane = (int)plane;
+        s.lds = (size_t)lds;
+        // workgroups per CU: by registers (3 of at most 168 a lane, or 2) and LDS
+        s.per_cu = (int)std::min<int64_t>(s.mb * s.nb <= 4 ? 3 : 2, device_max_lds() / lds);
+        const double products = 32.0 * s.mb * s.nb * ksteps;
+        const double words = (double)plane * p.cw / lce::kMfmaThreads;
+        const int64_t n = (s.tiles * s.groups + cus - 1) / cus;
+        const int vec = p.cw % 4 == 0 ? 4 : p.cw % 2 == 0 ? 2 : 1;
+        const int64_t elems = (int64_t)s.width * (p.cw / vec);
+        const int64_t units = elems <= 32 ? (s.tile_rows + 1) / 2 : s.tile_rows * ((elems + 63) / 64);
+        const int64_t waits = (units - 1) / (4 * lce::stream_reg_u(vec));   // loads not in flight
+        const double stage = 300.0 * words + 1500.0 * waits;
+        const double rest = 1000.0 + stage + 120.0 * s.mb * s.nb;
+        s.cost = 5000.0 + (s.nb == 1 ? 1500.0 : 0.0) + stage + 1.35 * products +
+                 (n - 1) * (s.per_cu > 1 ? rest + products : rest + 2000.0 + 1.35 * products);
+        if (!best.mb || s.cost < best.cost) best = s;
+    }
+    return best;
+}
+
+// Cycles of a K-split plan: a workgroup is alone on its CU where its LDS leaves
+// no room for another (7x7x512 batch 256, 5x5x256 64x64 batch 32: 17K and 20K a
+// workgroup measured), else its set-up hides behind another's products.
+double ks_cycles(const KsPlan &kp, int64_t cus, int64_t ksteps) {
+    const double products = 32.0 * kp.mbw * kp.nblk * ((ksteps + 3) / 4);
+    const int64_t n = (kp.wgs + cus - 1) / cus;
+    const bool alone = 2 * kp.lds > (size_t)device_max_lds();
+    return (alone ? 9300.0 : 6000.0) + 1.65 * products +
+           (n - 1) * ((alone ? 9300.0 : 2000.0) + 1.65 * products);
+}
+
+// Pixel-split schedule: MB pixel blocks of 32 per wave (128*MB pixels per
+// workgroup) and NBLK filter blocks of 32, one channel chunk widened at a
+// time (any region width that fits one chunk).  The largest tiles reuse each
+// operand read from LDS most; they are kept while the grid still covers every
+// CU.
+struct PxPlan {
+    int mb = 0, nblk = 0, tile_rows = 0;
+    int64_t wgs = 0;
+    size_t lds = 0, lds_static = 0;
+    bool fits = false;
+};
+
+PxPlan plan_mfma_pixel(const lce::MfmaParams &p, int64_t cus, int blocks32, int cc) {
+    PxPlan b;
+    const int nmax = blocks32 >= 4 ? 4 : blocks32 >= 2 ? 2 : 1;
+    static const int kSplits[][2] = {{2, 4}, {1, 4}, {2, 2}, {1, 2}, {2, 1}, {1, 1}};
+    b.mb = b.nblk = 1;
+    int64_t best_wgs = -1;
+    for (const auto &o : kSplits) {
+        if (o[1] > nmax) continue;
+        const int64_t wgs = ((int64_t)p.m + 128 * o[0] - 1) / (128 * o[0]) *
+                            ((blocks32 + o[1] - 1) / o[1]);
+        if (wgs >= cus) { b.mb = o[0]; b.nblk = o[1]; break; }
+        if (wgs > best_wgs) { best_wgs = wgs; b.mb = o[0]; b.nblk = o[1]; }
+    }
+    if (const int t = tuning(LCE_TUNE_MFMA_TILE_N)) b.nblk = t;
+    if (const int t = tuning(LCE_TUNE_MFMA_TILE_M)) b.mb = t;
+    if (b.nblk != 1 && b.nblk != 2 && b.nblk != 4) b.nblk = 4;
+    if (b.mb != 1 && b.mb != 2) b.mb = 2;
+    const int bm = 128 * b.mb;
+    b.tile_rows = mfma_tile_rows(p, bm);
+    b.wgs = ((int64_t)p.m + bm - 1) / bm * ((blocks32 + b.nblk - 1) / b.nblk);
+    // dynamic LDS: the widened A chunk, the packed input region (with the
+    // 256-word slack of its last DMA instruction), one byte per region row;
+    // the four B stages are static (4 x CC x 32*NBLK x 16 bytes)
+    const size_t region_words = (size_t)b.tile_rows * p.pw * p.cw;
+    b.lds = (size_t)cc * b.tile_rows * p.pw * 16 + (region_words + 256) * 4 +
+            ((size_t)b.tile_rows + 15) / 16 * 16;
+    b.lds_static = (size_t)4 * cc * 32 * b.nblk * 16;
+    b.fits = b.lds + b.lds_static <= (size_t)device_max_lds() &&
+             (int64_t)b.tile_rows * p.pw * cc <= INT32_MAX / 2;
+    return b;
+}
+
+void launch_px_plan(lce::MfmaParams &p, const lce_bconv2d_desc &d, const PxPlan &b, int blocks32,
+                    int cc, hipStream_t stream) {
+    p.tile_rows = b.tile_rows;
+    p.div_plane = lce::make_fastdiv((uint32_t)(b.tile_rows * p.pw));
+    const int bm = 128 * b.mb;
+    const dim3 grid((unsigned)(((int64_t)p.m + bm - 1) / bm),
+                    (unsigned)((blocks32 + b.nblk - 1) / b.nblk));
+    lce::launch_mfma_pixel(p, d.out_type, cc, b.nblk, b.mb, grid, b.lds, stream);
+}
+
+// Cycles of a pixel-split plan: a workgroup alone on its CU waits for each of
+// its K stages behind a barrier (5x5x32 18x20 batch 17: 13.3K predicted, 14K
+// measured); with others to overlap it the products, or the staging and the
+// output, count (5x5x64 91x52 batch 79: 60K, 57K; 1x1 28x28x256->512 batch 256:
+// 117K, 118K; 1x1 160->256 over 103K pixels: 35K, 36K).
+double px_cycles(const PxPlan &b, int64_t cus, int64_t ksteps) {
+    const double products = 32.0 * b.mb * b.nblk * ksteps;
+    const int64_t n = (b.wgs + cus - 1) / cus;
+    return 4500.0 + 250.0 * ksteps + 3.2 * products +
+           (n - 1) * std::max(1500.0 + 2.0 * products, 9000.0 * b.mb * b.nblk / 8);
+}
+
+// The geometry the streaming schedule works on: a 1x1 filter at stride 1 has
+// no window, and the batch is then one row of pixels (tiles of any run of
+// pixels, and no padding).
+lce::MfmaGeom stream_geometry(const lce::MfmaGeom &g) {
+    lce::MfmaGeom p = g;
+    if (p.kh == 1 && p.kw == 1 && p.sh == 1 && p.sw == 1) {
+        p.w = p.ow = p.pw = p.m;
+        p.n = p.h = p.oh = p.ph = 1;
+        p.div_ph = lce::make_fastdiv(1);
+    }
+    return p;
+}
+
+void launch_stream_plan(const lce::MfmaGeom &geom, const lce_bconv2d_desc &d, const StreamPlan &s,
+                        int64_t cus, int64_t ksteps, hipStream_t stream) {
+    lce::StreamParams p{};
+    static_cast<lce::MfmaGeom &>(p) = geom;
+    p.tiles = (int)s.tiles;
+    p.th = s.th;
+    p.tw = s.tw;
+    p.px = s.th * s.tw;
+    p.col_tiles = s.col_tiles;
+    p.wf = s.wf;
+    p.ksteps = (int)ksteps;
+    p.pad_sum = d.kh * d.kw * (32 * p.cwe - d.c_in);
+    for (int w = 0; w < 4; ++w) {
+        uint32_t f = 0;
+        for (int c = w; c < 32; c += 4)
+            if (d.c_in % 32 && c >= d.c_in % 32) f |= 2u << (c / 4 * 4);
+        p.pad_fill[w] = f;
+    }
+    p.tile_rows = s.tile_rows;
+    p.pw = s.width;
+    p.plane = s.plane;
+    p.region_vec = p.cw % 4 == 0 && aligned(p.x, 16) ? 4 : p.cw % 2 == 0 && aligned(p.x, 8) ? 2 : 1;
+    const int g = p.cw / p.region_vec;
+    p.row_elems = s.width * g;
+    p.row_pair = p.row_elems <= 32;
+    p.row_segs = (p.row_elems + 63) / 64;
+    p.units = p.row_pair ? (s.tile_rows + 1) / 2 : s.tile_rows * p.row_segs;
+    p.out8 = p.cwo % 2 == 0 && aligned(p.out, 8);
+    p.div_ct = lce::make_fastdiv((uint32_t)s.col_tiles);
+    p.div_tw = lce::make_fastdiv((uint32_t)s.tw);
+    p.div_oh = lce::make_fastdiv((uint32_t)p.oh);
+    p.div_g = lce::make_fastdiv((uint32_t)g);
+    p.div_segs = lce::make_fastdiv((uint32_t)p.row_segs);
+    const int t = tuning(LCE_TUNE_MFMA_FS_WPC);
+    const int64_t slots = std::max<int64_t>(1, cus * (t == 1 || t == 2 ? t : s.per_cu) / s.groups);
+    const dim3 grid((unsigned)std::min(slots, s.tiles), (unsigned)s.groups);
+    lce::launch_mfma_stream(p, d.out_type, s.mb, s.nb, grid, s.lds, stream);
 }
 
 }  // namespace
@@ -1208,82 +1439,63 @@ lce_status lce_bconv2d_mfma(const lce_bconv2d_desc *desc, const int32_t *x_packe
     mfma_chunk(p.cw, &cc, &cwe);
     const int64_t cus = device_simds() / 4;
     const int blocks32 = p.coutp / 32;
-    const int nmax = blocks32 >= 4 ? 4 : blocks32 >= 2 ? 2 : 1;
-
-    // K-split schedule (all four waves on one tile, K divided among them),
-    // for long K: it widens the whole input region up front and ends with a
-    // reduction, which pay off from about 5 K steps per wave on (measured
-    // on the batch-1 sweep layers with 25 and 27 K steps, which no
-    // filter-stationary instance covers within 1/8 padding: 3.7-5.7 us
-    // against 7.4-10.2 us on the pixel split, whose K stages run one after
-    // another behind barriers).  The tile is 32*MBW pixels x 32*NBLK
-    // filters: the largest (at most eight 32x32 blocks) whose grid still
-    // gives every CU 1.5 workgroups, among those whose LDS fits.  The
-    // mfma_schedule tuning key forces either schedule (the K-split one where
-    // its LDS fits).
     const int64_t ksteps = (int64_t)d.kh * d.kw * (p.cwe / 2);
-    // 0 auto, 1 filter-stationary, 2 K split, 3 pixel split
+    // 0 auto, 1 filter-stationary, 2 K split, 3 pixel split, 4 streaming
     const int sched = tuning(LCE_TUNE_MFMA_SCHEDULE);
-    const int ks_env = sched == 2 ? 1 : sched == 3 ? 0 : -1;
 
-    // Filter-stationary schedule: the default wherever an instance fits, up
-    // to 36 K steps.  Longer K runs on the K-split schedule below unless an
-    // instance is forced (tuning keys mfma_fs_ks and mfma_fs_s): with S = 4
-    // waves per filter block every filter group re-widens the same input
-    // region and the partial sums add LDS traffic, measured slower than the
-    // K split on the 7x7x512 layer.  The mfma_schedule key forces one of the
-    // others.
+    // Filter-stationary: wherever an instance fits, up to 36 K steps (up to
+    // 72 when an instance is forced through mfma_fs_ks and mfma_fs_s: with
+    // S = 4 waves per filter block every filter group re-widens the same input
+    // region and the partial sums add LDS traffic, measured slower than the K
+    // split on the 7x7x512 layer).  The others take what it does not: the K
+    // split where K is long or few tiles fill the CUs, else the pixel split.
     const bool fs_forced = tuning(LCE_TUNE_MFMA_FS_KS) && tuning(LCE_TUNE_MFMA_FS_S);
-    if (ks_env < 0 &&
-        (ksteps <= 36 || (fs_forced && ksteps <= 72))) {
-        if (launch_fs_plan(p, d, cus, blocks32, ksteps, false, stream))
-            return check_launch("lce_bconv2d_mfma launch");
-    }
+    const bool fs_k = (sched == 0 || sched == 1 || sched == 4) &&
+                      (ksteps <= 36 || (fs_forced && ksteps <= 72));
+    const FsPlan fp = fs_k ? plan_mfma_fs(p, cus, blocks32, (int)ksteps) : FsPlan{};
+    const bool ks_k = sched == 2 || (sched != 3 && !fp.shape.ks);
+    const KsPlan kp = ks_k ? plan_mfma_ks(p, cus, blocks32) : KsPlan{};
+    const bool px_k = !fp.shape.ks;
+    const PxPlan pp = px_k ? plan_mfma_pixel(p, cus, blocks32, cc) : PxPlan{};
 
-    if (ks_env == 1 || (ks_env != 0 && ksteps >= 20)) {
-        if (launch_ks_plan(p, d, plan_mfma_ks(p, cus, blocks32), blocks32, false, stream))
-            return check_launch("lce_bconv2d_mfma launch");
-    }
-
-    // Pixel-split schedule: MB pixel blocks of 32 per wave (128*MB pixels
-    // per workgroup) and NBLK filter blocks of 32, one channel chunk widened
-    // at a time (any region width that fits one chunk).  The largest tiles
-    // reuse each operand read from LDS most; they are kept while the grid
-    // still covers every CU.
-    static const int kSplits[][2] = {{2, 4}, {1, 4}, {2, 2}, {1, 2}, {2, 1}, {1, 1}};
-    int mb = 1, nblk = 1;
-    int64_t best_wgs = -1;
-    for (const auto &o : kSplits) {
-        if (o[1] > nmax) continue;
-        const int64_t wgs = ((int64_t)p.m + 128 * o[0] - 1) / (128 * o[0]) *
-                            ((blocks32 + o[1] - 1) / o[1]);
-        if (wgs >= cus) { mb = o[0]; nblk = o[1]; break; }
-        if (wgs > best_wgs) { best_wgs = wgs; mb = o[0]; nblk = o[1]; }
-    }
-    if (const int t = tuning(LCE_TUNE_MFMA_TILE_N)) nblk = t;
-    if (const int t = tuning(LCE_TUNE_MFMA_TILE_M)) mb = t;
-    if (nblk != 1 && nblk != 2 && nblk != 4) nblk = 4;
-    if (mb != 1 && mb != 2) mb = 2;
-    const int bm = 128 * mb;
-    p.tile_rows = mfma_tile_rows(p, bm);
-    p.div_plane = lce::make_fastdiv((uint32_t)(p.tile_rows * p.pw));
-    const int64_t pix_groups = ((int64_t)p.m + bm - 1) / bm;
-    // dynamic LDS: the widened A chunk, the packed input region (with the
-    // 256-word slack of its last DMA instruction), one byte per region row;
-    // the four B stages are static (4 x CC x 32*NBLK x 16 bytes)
-    const size_t region_words = (size_t)p.tile_rows * p.pw * p.cw;
-    const size_t lds = (size_t)cc * p.tile_rows * p.pw * 16 + (region_words + 256) * 4 +
-                       ((size_t)p.tile_rows + 15) / 16 * 16;
-    const size_t lds_static = (size_t)4 * cc * 32 * nblk * 16;
-    if (lds + lds_static > (size_t)device_max_lds())
+    // What none of the three takes is refused, also where the streaming
+    // schedule's column tiles would do (the header documents the limit).
+    const bool ks_takes = kp.mbw && (sched == 2 || ksteps >= 20);
+    if (!fp.shape.ks && !ks_takes && !pp.fits)
         return fail(LCE_EUNSUPPORTED,
                     "matrix-core tile of %zu bytes exceeds the %d bytes of LDS per workgroup "
-                    "(padded width %d, %d rows)", lds + lds_static, device_max_lds(), p.pw,
-                    p.tile_rows);
-    if ((int64_t)p.tile_rows * p.pw * cc > INT32_MAX / 2)
-        return fail(LCE_EUNSUPPORTED, "matrix-core tile too large");
-    const dim3 grid((unsigned)pix_groups, (unsigned)((blocks32 + nblk - 1) / nblk));
-    lce::launch_mfma_pixel(p, d.out_type, cc, nblk, mb, grid, lds, stream);
+                    "(padded width %d, %d rows)", pp.lds + pp.lds_static, device_max_lds(), p.pw,
+                    pp.tile_rows);
+
+    // Streaming: where its price is below that of the schedule it replaces.
+    enum { FS, KS, PX } other = fp.shape.ks ? FS : ks_takes ? KS : PX;
+    if (sched == 0 && other != FS && kp.mbw && pp.fits &&
+        !tuning(LCE_TUNE_MFMA_TILE_M) && !tuning(LCE_TUNE_MFMA_TILE_N))
+        other = ks_cycles(kp, cus, ksteps) <= px_cycles(pp, cus, ksteps) ? KS : PX;
+    // (not where a tuning key asks for something of the others)
+    bool keys = false;
+    for (const lce_tuning_key k : {LCE_TUNE_MFMA_FS_KS, LCE_TUNE_MFMA_FS_S, LCE_TUNE_MFMA_FS_WPC,
+                                   LCE_TUNE_MFMA_FS_PAD, LCE_TUNE_MFMA_PACKED,
+                                   LCE_TUNE_MFMA_TILE_M, LCE_TUNE_MFMA_TILE_N,
+                                   LCE_TUNE_MFMA_FS_WINDOW})
+        keys = keys || tuning(k);
+    if (sched == 4 || (sched == 0 && !keys)) {
+        const lce::MfmaGeom sg = stream_geometry(p);
+        const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32);
+        const double price = other == FS   ? fs_cycles(fp)
+                             : other == KS ? ks_cycles(kp, cus, ksteps)
+                                           : px_cycles(pp, cus, ksteps);
+        if (sp.mb && (sched == 4 || sp.cost < price)) {
+            launch_stream_plan(sg, d, sp, cus, ksteps, stream);
+            return check_launch("lce_bconv2d_mfma launch");
+        }
+    }
+    if (other == FS)
+        launch_fs_plan(p, d, fp, cus, blocks32, ksteps, false, stream);
+    else if (other == KS)
+        launch_ks_plan(p, d, kp, blocks32, false, stream);
+    else
+        launch_px_plan(p, d, pp, blocks32, cc, stream);
     return check_launch("lce_bconv2d_mfma launch");
 }
 
@@ -1339,7 +1551,8 @@ lce_status lce_quantize_bconv2d_mfma(const lce_bconv2d_desc *desc, const float *
         const KsPlan kp = ks_k ? plan_mfma_ks(p, cus, blocks32) : KsPlan{};
         const bool fs_first =
             fs_k && (ksteps <= 36 || sched == 1 || !kp.mbw || kp.wgs < cus);
-        if ((fs_first && launch_fs_plan(p, d, cus, blocks32, ksteps, true, stream)) ||
+        if ((fs_first && launch_fs_plan(p, d, plan_mfma_fs(p, cus, blocks32, (int)ksteps), cus, blocks32,
+                                        ksteps, true, stream)) ||
             (ks_k && launch_ks_plan(p, d, kp, blocks32, true, stream)))
             return check_launch("lce_quantize_bconv2d_mfma launch");
     }
