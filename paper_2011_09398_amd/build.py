@@ -21,7 +21,7 @@ PROBE_LIB = os.path.join(PKG, "libprobe.so")
 PROBE_SOURCES = [os.path.join(CSRC, "valu_probe.hip")]
 HEADERS = [os.path.join(CSRC, f) for f in ("bitpack.hpp", "bconv.hpp", "pool.hpp",
                                                  "bconv_mfma.hpp", "launch.hpp", "mfma_fs_launch.hpp", "dpp.hpp",
-                                                 "bconv_quant.hpp", "bconv_mfma_stream.hpp")] + \
+                                                 "bconv_quant.hpp", "bconv_mfma_stream.hpp", "fastdiv.hpp")] + \
           [os.path.join(INCLUDE, "lce.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -55,6 +55,8 @@
 #include <climits>
 #include <type_traits>
 
+#include "fastdiv.hpp"
+
 namespace lce {
 
 enum OutKind : int { OUT_FLOAT = 0, OUT_BITS = 1, OUT_INT = 2 };
@@ -69,23 +71,6 @@ constexpr int kMaxFiltersWG = kWaves * kMaxNB * kRN;   // 128
 constexpr int kSlabWords = 160;   // generic kernel: im2col words staged per pass
 constexpr int kNever = INT32_MAX;   // zero-padding bound that no accumulator reaches
 constexpr int kAlways = INT32_MIN;  // zero-padding bound that every accumulator reaches
-
-// Unsigned division n / d for n < 2^31 by multiply-high (Granlund-Montgomery
-// round-up variant): q = (mulhi(n, magic) + n) >> shift.
-struct FastDiv {
-    uint32_t d, magic, shift;
-};
-
-__host__ inline FastDiv make_fastdiv(uint32_t d) {
-    uint32_t l = 0;
-    while ((1ull << l) < d) ++l;                       // l = ceil(log2 d)
-    const uint64_t magic = ((1ull << 32) * ((1ull << l) - d)) / d + 1;
-    return FastDiv{d, (uint32_t)magic, l};
-}
-
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv &f) {
-    return (__umulhi(n, f.magic) + n) >> f.shift;
-}
 
 struct BconvParams {
     const uint32_t *x;      // [N][H][W][Cw]

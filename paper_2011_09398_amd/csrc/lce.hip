@@ -1089,11 +1089,15 @@ lce_status lce_bitpack(const float *x, int32_t *out, int64_t rows, int32_t chann
                            reinterpret_cast<const float4 *>(x), reinterpret_cast<uint32_t *>(out),
                            nwords);
     } else {
-        int64_t blocks = (nwords + lce::kBitpackThreads - 1) / lce::kBitpackThreads;
-        if (blocks > 256 * 32) blocks = 256 * 32;
+        // words per workgroup pass: enough workgroups for the CUs (four each),
+        // then as many words as the LDS string holds
+        int64_t chunk = (nwords + 1023) / 1024;
+        chunk = std::min<int64_t>(std::max<int64_t>((chunk + 63) / 64 * 64, 64), lce::kBitpackChunk);
+        const int64_t blocks = std::min<int64_t>((nwords + chunk - 1) / chunk, 256 * 16);
         hipLaunchKernelGGL(lce::bitpack_generic_kernel, dim3((unsigned)blocks),
                            dim3(lce::kBitpackThreads), 0, stream, x,
-                           reinterpret_cast<uint32_t *>(out), rows, (int)channels, cw);
+                           reinterpret_cast<uint32_t *>(out), rows, (int)channels, (int)chunk,
+                           lce::make_fastdiv((uint32_t)cw));
     }
     return check_launch("lce_bitpack launch");
 }
@@ -1365,12 +1369,18 @@ lce_status lce_dequantize(const int32_t *x_packed, float *out, int64_t rows, int
                            reinterpret_cast<const uint32_t *>(x_packed),
                            reinterpret_cast<float4 *>(out), n4);
     } else {
-        int64_t blocks = (count + lce::kPoolThreads - 1) / lce::kPoolThreads;
-        if (blocks > 256 * 16) blocks = 256 * 16;
-        hipLaunchKernelGGL(lce::dequantize_generic_kernel, dim3((unsigned)blocks),
-                           dim3(lce::kPoolThreads), 0, stream,
-                           reinterpret_cast<const uint32_t *>(x_packed), out, count, channels,
-                           packed_words(channels));
+        const int64_t blocks =
+            std::min<int64_t>((count + lce::kDequantChunk - 1) / lce::kDequantChunk, 256 * 64);
+        const lce::FastDiv div = lce::make_fastdiv((uint32_t)channels);
+        const int cw = packed_words(channels);
+        if (aligned(out, 16))
+            hipLaunchKernelGGL(lce::dequantize_generic_kernel<4>, dim3((unsigned)blocks),
+                               dim3(lce::kPoolThreads), 0, stream,
+                               reinterpret_cast<const uint32_t *>(x_packed), out, count, cw, div);
+        else
+            hipLaunchKernelGGL(lce::dequantize_generic_kernel<1>, dim3((unsigned)blocks),
+                               dim3(lce::kPoolThreads), 0, stream,
+                               reinterpret_cast<const uint32_t *>(x_packed), out, count, cw, div);
     }
     return check_launch("lce_dequantize launch");
 }

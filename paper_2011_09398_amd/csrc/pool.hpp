@@ -114,16 +114,62 @@ __global__ __launch_bounds__(kPoolThreads) void dequantize32_kernel(const uint32
     }
 }
 
-// Dequantize, any channel count: one output float per thread.
+// Dequantize, any channel count: VEC consecutive output floats per thread (4,
+// 16-byte stores, where out is 16-byte aligned; else 1), which may lie in
+// several words and rows.  A workgroup takes kDequantChunk consecutive floats
+// at a time, so that the row of each is a 32-bit division from the first one's.
+// (One float per thread with a 64-bit division: 64 images of 56x56x72, 60 MB,
+// 18.8 us; this 12 us.)
+constexpr int kDequantChunk = 4096;
+
+template <int VEC>
 __global__ __launch_bounds__(kPoolThreads) void dequantize_generic_kernel(
-    const uint32_t *__restrict__ x, float *__restrict__ out, int64_t count, int channels,
-    int cw) {
-    const int64_t stride = (int64_t)gridDim.x * kPoolThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kPoolThreads + threadIdx.x; i < count; i += stride) {
-        const int64_t r = i / channels;
-        const int c = (int)(i - r * channels);
-        const uint32_t bit = (x[r * cw + (c >> 5)] >> (c & 31)) & 1u;
-        out[i] = __uint_as_float(0x3F800000u | bit << 31);
+    const uint32_t *__restrict__ x, float *__restrict__ out, int64_t count, int cw,
+    FastDiv div_c) {
+    const int channels = (int)div_c.d;
+    for (int64_t f0 = (int64_t)blockIdx.x * kDequantChunk; f0 < count;
+         f0 += (int64_t)gridDim.x * kDequantChunk) {
+        const int64_t r0 = f0 / channels;
+        const uint32_t c0 = (uint32_t)(f0 - r0 * channels);
+        const uint32_t *xr = x + r0 * cw;
+        const int n = (int)min((int64_t)kDequantChunk, count - f0);
+#pragma unroll
+        for (int u = 0; u < kDequantChunk / (VEC * kPoolThreads); ++u) {
+            const int i = (u * kPoolThreads + (int)threadIdx.x) * VEC;
+            if (i >= n) break;
+            // (at most one row end where rows are longer than the chunk; the sum
+            // may pass the division's 2^31 only there)
+            uint32_t r = channels >= kDequantChunk ? (c0 + i >= (uint32_t)channels)
+                                                   : fast_div(c0 + i, div_c);
+            uint32_t c = c0 + i - r * channels;
+            uint32_t v[VEC];
+            if (VEC == 4 && (c & 31) <= 28 && c + 4 <= (uint32_t)channels) {
+                // one word holds all four (the chunk's end is a row's end or later)
+                const uint32_t w = xr[(int64_t)r * cw + (c >> 5)] >> (c & 31);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) v[e] = 0x3F800000u | (w >> e) << 31;
+            } else {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    // (past the end: the first word again, not stored)
+                    const int64_t at = i + e < n ? (int64_t)r * cw + (c >> 5) : 0;
+                    v[e] = 0x3F800000u | (xr[at] >> (c & 31)) << 31;
+                    if (++c == (uint32_t)channels) {
+                        c = 0;
+                        ++r;
+                    }
+                }
+            }
+            if constexpr (VEC == 4) {
+                if (i + 4 <= n) {
+                    *reinterpret_cast<uint4 *>(out + f0 + i) = make_uint4(v[0], v[1], v[2], v[3]);
+                    continue;
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < VEC; ++e)
+                if (i + e < n) reinterpret_cast<uint32_t *>(out)[f0 + i + e] = v[e];
+        }
     }
 }
 
