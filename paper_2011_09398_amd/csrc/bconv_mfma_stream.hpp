@@ -305,7 +305,7 @@ __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mf
         int a_base[MB];
 #pragma unroll
         for (int b = 0; b < MB; ++b) a_base[b] = (int)(pix[b] & 0xFFFFu);
-        if (tile.oy0 + p.th > p.oh) {
+        if (p.n > 1 && tile.oy0 + p.th > p.oh) {
             const int gap = (p.ph - p.oh * p.sh) * PW;
 #pragma unroll
             for (int b = 0; b < MB; ++b)

@@ -496,7 +496,7 @@ int device_max_lds() { return device_attribute<hipDeviceAttributeMaxSharedMemory
 // images are further apart than their output rows, once per image boundary
 // that `rows` rows can cross (`aligned`: they start at a multiple of `rows`).
 int64_t padded_rows(const lce::MfmaGeom &p, int64_t rows, bool aligned) {
-    int64_t cross = rows > 1 ? (rows - 2) / p.oh + 1 : 0;
+    int64_t cross = rows > 1 && p.n > 1 ? (rows - 2) / p.oh + 1 : 0;
     if (aligned && p.oh % rows == 0) cross = 0;
     if (aligned && rows % p.oh == 0) cross = rows / p.oh - 1;
     const int64_t gap = std::max<int64_t>(0, (int64_t)p.ph - (int64_t)p.oh * p.sh);
@@ -508,6 +508,7 @@ int64_t padded_rows(const lce::MfmaGeom &p, int64_t rows, bool aligned) {
 // the search ends where it meets the bound of bm pixels anywhere, as it
 // mostly does within a few workgroups).
 int mfma_tile_rows(const lce::MfmaGeom &p, int bm) {
+    if (p.ow % bm == 0) return p.kh;             // every workgroup within one output row
     const int64_t per_img = (int64_t)p.oh * p.ow;
     const int64_t blocks = ((int64_t)p.m + bm - 1) / bm;
     const int64_t period = per_img / std::gcd<int64_t>(per_img, bm);   // blocks until it repeats
