@@ -267,8 +267,8 @@ lce_status lce_bconv2d_mfma(const lce_bconv2d_desc *desc, const int32_t *x_packe
  * and bitpacked, then convolved).  The result equals lce_bitpack of x
  * followed by lce_bconv2d_mfma (and so lce_bconv2d) on the packed tensor,
  * bit for bit, with no packed copy written to memory: each workgroup of the
- * filter-stationary or the K-split schedule binarizes the input region its
- * windows read while staging it.
+ * filter-stationary, the K-split or the streaming schedule binarizes the
+ * input region its windows read while staging it.
  *   x          float32 [N][H][W][C_in]  (device, 16-byte aligned); the sign
  *              test is lce_bitpack's (x < 0.0f is a 1 bit = -1.0, so -0.0
  *              and NaN give +1.0)
@@ -282,8 +282,8 @@ lce_status lce_bconv2d_mfma(const lce_bconv2d_desc *desc, const int32_t *x_packe
  * filters over few channels) return LCE_EUNSUPPORTED before anything is
  * launched, and the caller runs lce_bitpack and lce_bconv2d_mfma instead.
  * LCE_TUNE_MFMA_SCHEDULE 1 or 2 restricts the choice to that schedule (2
- * then takes any K); 3 and 4, the pixel split and the streaming schedule,
- * have no fused form and are refused.
+ * then takes any K); 4 takes the streaming schedule for the shapes covered
+ * above; 3, the pixel split, has no fused form and is refused.
  * Errors: as lce_bconv2d_mfma, plus LCE_EUNSUPPORTED (above) and LCE_EALIGN
  *         for an x that is not 16-byte aligned. */
 lce_status lce_quantize_bconv2d_mfma(const lce_bconv2d_desc *desc, const float *x,
@@ -345,7 +345,7 @@ typedef enum {
     LCE_TUNE_MFMA_SCHEDULE = 2,   /* lce_bconv2d_mfma and lce_quantize_bconv2d_mfma:
                                      1 filter-stationary (where an instance fits),
                                      2 K split, 3 pixel split (not fused), 4 streaming
-                                     (where a tile fits; not fused)                     */
+                                     (where a tile fits)                                */
     LCE_TUNE_MFMA_FS_KS = 3,      /* filter-stationary instance: K steps per wave       */
     LCE_TUNE_MFMA_FS_S = 4,       /* filter-stationary instance: waves per filter block */
     LCE_TUNE_MFMA_FS_WPC = 5,     /* filter-stationary and streaming grids: 1 or 2 workgroups

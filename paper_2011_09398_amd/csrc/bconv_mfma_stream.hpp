@@ -30,7 +30,9 @@
 // Measured (us; the schedule that took the layer before, and this one):
 // 56x56x64->64 batch 256 44.9 -> 21.5, 14x14x256 batch 256 42 -> 15.8,
 // 7x7x512 batch 256 32.7 -> 16.8, 1x1 28x28x256->512 batch 256 58 -> 30,
-// 5x5 64x64x256 batch 32 (float) 155 -> 85, 3x3 360x640x64 x2 (float) 46 -> 26.
+// 5x5 64x64x256 batch 32 (float) 155 -> 85, 3x3 360x640x64 x2 (float) 46 -> 26;
+// from float32 input 56x56x64->64 batch 256 (212 MB) 65 -> 48, 28x28x128 batch
+// 128 with float output (103 MB) 28.5 -> 23, 14x14x256 batch 256 90 -> 27.
 // What bounds it: 56x56x64 spends 13.5K of 37K cycles per wave in the
 // products, the rest in staging, output and waiting; with long K (5x5x256) it
 // is the matrix pipe at the clock that random +-1 data leave it (about 8
@@ -59,7 +61,7 @@ struct StreamParams : MfmaGeom {
 };
 
 // wave loads of the region that a wave holds in flight
-constexpr int stream_reg_u(int v) { return v == 1 ? 8 : 4; }
+constexpr int stream_reg_u(int v) { return v == 0 ? 0 : v == 1 ? 8 : 4; }
 
 // Where a tile lies: output row rr0 of the batch = row oy0 of image img0, column x0.
 struct StreamTile {
@@ -68,7 +70,7 @@ struct StreamTile {
 
 template <int V>
 struct StreamRegion {
-    uint32_t w[stream_reg_u(V) * V];
+    uint32_t w[V == 0 ? 1 : stream_reg_u(V) * V];
     uint32_t out;                    // bit u: the lane's element of load u lies outside the image
 };
 
@@ -187,8 +189,67 @@ __device__ __forceinline__ void stream_widen(const StreamParams &p, const Stream
     }
 }
 
+// LceQuantize fused into the staging: the input is float32, and a wave packs 64
+// words (8 KiB) at a time, eight loads of 1 KiB each, consecutive lanes on
+// consecutive 16 bytes.  A lane's four signs make a nibble (x < 0, the bitpack
+// kernel's test), three DPP ORs the word of its eight lanes, and lane 8g + k
+// keeps word 8k + g of the 64, widens it and writes it to the A tile.  (Giving a lane the 128 bytes of a word, as
+// the other schedules do, touches 64 cache lines per load instruction: the
+// 56x56x64->64 layer at batch 256, 205 MB in, 65 us there, 48 here.)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+
+__device__ __forceinline__ void stream_quantize(const StreamParams &p, const StreamTile &t,
+                                                u32x4 *atile, int wave, int lane) {
+    const __amdgpu_buffer_rsrc_t xb =
+        buffer_of(p.x, (uint32_t)p.n * p.h * p.w * p.cw * 128u);
+    const int k8 = lane & 7, g8 = lane >> 3;
+    const int first = (t.x0 * p.sw - p.pl) * p.cw;       // the region row's first word in its image row
+    const int row_words = p.w * p.cw;
+    for (int unit = wave; unit < p.units; unit += 4) {
+        const int r = (int)fast_div((uint32_t)unit, p.div_segs);
+        const int e0 = (unit - r * p.row_segs) * 64;
+        int base;
+        const bool row_in = stream_row(p, t, r, base);   // (bytes of packed words; floats: 32 times)
+        uint32_t word = 0;
+        if (row_in) {
+            f32x4_t v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int e = e0 + 8 * k + g8;
+                const bool in = e < p.row_elems && (unsigned)(first + e) < (unsigned)row_words;
+                const auto x = __builtin_amdgcn_raw_buffer_load_b128(
+                    xb, in ? (first + e) * 128 + k8 * 16 : kBufOutside, base * 32, 0);
+                v[k] = f32x4_t{__uint_as_float(x[0]), __uint_as_float(x[1]),
+                               __uint_as_float(x[2]), __uint_as_float(x[3])};
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const f32x4_t f = v[k];
+                uint32_t s = ((uint32_t)(f.x < 0.0f) | ((uint32_t)(f.y < 0.0f) << 1) |
+                              ((uint32_t)(f.z < 0.0f) << 2) | ((uint32_t)(f.w < 0.0f) << 3))
+                             << (4 * k8);
+                s |= dpp_move<0xB1>(s);                  // quad_perm [1,0,3,2]
+                s |= dpp_move<0x4E>(s);                  // quad_perm [2,3,0,1]
+                s |= dpp_move<0x141>(s);                 // row_half_mirror
+                word = k8 == k ? s : word;
+            }
+        }
+        const int e = e0 + 8 * k8 + g8;
+        if (e < p.row_elems) {
+            const int c = (int)fast_div((uint32_t)e, p.div_g), j = e - c * p.cw;
+            const bool in = row_in && (unsigned)(first + e) < (unsigned)row_words;
+            atile[j * p.plane + r * p.pw + c] =
+                widen_word(word, p.pad_zero && !in ? 0u : kFp4PlusOne);
+        }
+    }
+}
+
 // OUT: output kind.  MB x NB blocks of 32 pixels x 32 filters per wave; p.wf of the four waves
-// side by side over filters, the others over pixels.  V: words per region load.
+// side by side over filters, the others over pixels.  V: words per region load,
+// 0 for a float32 input.
 template <int OUT, int MB, int NB, int V>
 __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mfma_stream_kernel(
     StreamParams p) {
@@ -219,7 +280,7 @@ __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mf
     int t = blockIdx.x;
     StreamTile tile = origin(t);
     StreamRegion<V> rch;
-    stream_load<V>(p, tile, wave, lane, 0, rch);
+    if constexpr (V > 0) stream_load<V>(p, tile, wave, lane, 0, rch);
     const __amdgpu_buffer_rsrc_t wb = filter_buffer(p, true);
     int col[NB];
 #pragma unroll
@@ -295,11 +356,15 @@ __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mf
         int lanev = lane, wavev = wave;
         asm volatile("" : "+v"(lanev), "+s"(wavev));
         // ---- the region of the tile
-        stream_widen<V>(p, rch, atile, wavev, lanev, 0);
-        for (int u0 = stream_reg_u(V); wavev + 4 * u0 < p.units; u0 += stream_reg_u(V)) {
-            StreamRegion<V> ch;
-            stream_load<V>(p, tile, wavev, lanev, u0, ch);
-            stream_widen<V>(p, ch, atile, wavev, lanev, u0);
+        if constexpr (V == 0) {
+            stream_quantize(p, tile, atile, wavev, lanev);
+        } else {
+            stream_widen<V>(p, rch, atile, wavev, lanev, 0);
+            for (int u0 = stream_reg_u(V); wavev + 4 * u0 < p.units; u0 += stream_reg_u(V)) {
+                StreamRegion<V> ch;
+                stream_load<V>(p, tile, wavev, lanev, u0, ch);
+                stream_widen<V>(p, ch, atile, wavev, lanev, u0);
+            }
         }
         // windows below an image boundary lie further down
         int a_base[MB];
@@ -318,7 +383,7 @@ __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mf
         const bool more = t < p.tiles;
         if (more) {
             tile = origin(t);
-            stream_load<V>(p, tile, wavev, lanev, 0, rch);
+            if constexpr (V > 0) stream_load<V>(p, tile, wavev, lanev, 0, rch);
         }
 
         const float *thr_z = thrs + z;

@@ -862,7 +862,8 @@ double fs_cycles(const FsPlan &fp) {
 // two blocks per wave: 45K, predicted 41K; 28x28x128 batch 256: 30K, 36K;
 // 14x14x256 batch 64: 11K, 10.9K; 7x7x512 batch 256: 31K, 30K; 1x1
 // 28x28x256->512 batch 256: 55K, 67K).  mb == 0: no tile fits the LDS.
-StreamPlan plan_stream(const lce::MfmaGeom &p, int64_t cus, int64_t ksteps, int blocks32) {
+StreamPlan plan_stream(const lce::MfmaGeom &p, int64_t cus, int64_t ksteps, int blocks32,
+                       bool qf) {
     StreamPlan best;
     const int force_mb = tuning(LCE_TUNE_MFMA_TILE_M), force_bn = tuning(LCE_TUNE_MFMA_TILE_N);
     // {mb, nb, wf}
@@ -913,8 +914,15 @@ StreamPlan plan_stream(const lce::MfmaGeom &p, int64_t cus, int64_t ksteps, int 
         const int64_t elems = (int64_t)s.width * (p.cw / vec);
         const int64_t units = elems <= 32 ? (s.tile_rows + 1) / 2 : s.tile_rows * ((elems + 63) / 64);
         const int64_t waits = (units - 1) / (4 * lce::stream_reg_u(vec));   // loads not in flight
-        const double stage = 300.0 * words + 1500.0 * waits;
-        const double rest = 1000.0 + stage + 120.0 * s.mb * s.nb;
+        double stage = 300.0 * words + 1500.0 * waits, stage_more = stage;
+        if (qf) {
+            // a float32 region: rounds of 64 words per wave, each a memory
+            // latency when alone; with others loading, the memory rate
+            const int64_t rounds = (s.tile_rows * (((int64_t)s.width * p.cw + 63) / 64) + 3) / 4;
+            stage = std::max(1000.0, 1900.0 * rounds - 3000.0);
+            stage_more = (s.per_cu > 2 ? 1500.0 : 1800.0) * words;
+        }
+        const double rest = 1000.0 + stage_more + 120.0 * s.mb * s.nb;
         s.cost = 5000.0 + (s.nb == 1 ? 1500.0 : 0.0) + stage + 1.35 * products +
                  (n - 1) * (s.per_cu > 1 ? rest + products : rest + 2000.0 + 1.35 * products);
         if (!best.mb || s.cost < best.cost) best = s;
@@ -999,6 +1007,17 @@ double px_cycles(const PxPlan &b, int64_t cus, int64_t ksteps) {
            (n - 1) * std::max(1500.0 + 2.0 * products, 9000.0 * b.mb * b.nblk / 8);
 }
 
+// Whether a tuning key asks for a tile, an instance or a grid of the other
+// schedules.
+bool other_keys() {
+    for (const lce_tuning_key k : {LCE_TUNE_MFMA_FS_KS, LCE_TUNE_MFMA_FS_S, LCE_TUNE_MFMA_FS_WPC,
+                                   LCE_TUNE_MFMA_FS_PAD, LCE_TUNE_MFMA_PACKED,
+                                   LCE_TUNE_MFMA_TILE_M, LCE_TUNE_MFMA_TILE_N,
+                                   LCE_TUNE_MFMA_FS_WINDOW})
+        if (tuning(k)) return true;
+    return false;
+}
+
 // The geometry the streaming schedule works on: a 1x1 filter at stride 1 has
 // no window, and the batch is then one row of pixels (tiles of any run of
 // pixels, and no padding).
@@ -1013,7 +1032,7 @@ lce::MfmaGeom stream_geometry(const lce::MfmaGeom &g) {
 }
 
 void launch_stream_plan(const lce::MfmaGeom &geom, const lce_bconv2d_desc &d, const StreamPlan &s,
-                        int64_t cus, int64_t ksteps, hipStream_t stream) {
+                        int64_t cus, int64_t ksteps, bool qf, hipStream_t stream) {
     lce::StreamParams p{};
     static_cast<lce::MfmaGeom &>(p) = geom;
     p.tiles = (int)s.tiles;
@@ -1033,10 +1052,11 @@ void launch_stream_plan(const lce::MfmaGeom &geom, const lce_bconv2d_desc &d, co
     p.tile_rows = s.tile_rows;
     p.pw = s.width;
     p.plane = s.plane;
-    p.region_vec = p.cw % 4 == 0 && aligned(p.x, 16) ? 4 : p.cw % 2 == 0 && aligned(p.x, 8) ? 2 : 1;
-    const int g = p.cw / p.region_vec;
+    p.region_vec = qf ? 0 : p.cw % 4 == 0 && aligned(p.x, 16) ? 4
+                          : p.cw % 2 == 0 && aligned(p.x, 8) ? 2 : 1;
+    const int g = qf ? p.cw : p.cw / p.region_vec;
     p.row_elems = s.width * g;
-    p.row_pair = p.row_elems <= 32;
+    p.row_pair = !qf && p.row_elems <= 32;
     p.row_segs = (p.row_elems + 63) / 64;
     p.units = p.row_pair ? (s.tile_rows + 1) / 2 : s.tile_rows * p.row_segs;
     p.out8 = p.cwo % 2 == 0 && aligned(p.out, 8);
@@ -1484,20 +1504,14 @@ lce_status lce_bconv2d_mfma(const lce_bconv2d_desc *desc, const int32_t *x_packe
         !tuning(LCE_TUNE_MFMA_TILE_M) && !tuning(LCE_TUNE_MFMA_TILE_N))
         other = ks_cycles(kp, cus, ksteps) <= px_cycles(pp, cus, ksteps) ? KS : PX;
     // (not where a tuning key asks for something of the others)
-    bool keys = false;
-    for (const lce_tuning_key k : {LCE_TUNE_MFMA_FS_KS, LCE_TUNE_MFMA_FS_S, LCE_TUNE_MFMA_FS_WPC,
-                                   LCE_TUNE_MFMA_FS_PAD, LCE_TUNE_MFMA_PACKED,
-                                   LCE_TUNE_MFMA_TILE_M, LCE_TUNE_MFMA_TILE_N,
-                                   LCE_TUNE_MFMA_FS_WINDOW})
-        keys = keys || tuning(k);
-    if (sched == 4 || (sched == 0 && !keys)) {
+    if (sched == 4 || (sched == 0 && !other_keys())) {
         const lce::MfmaGeom sg = stream_geometry(p);
-        const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32);
+        const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32, false);
         const double price = other == FS   ? fs_cycles(fp)
                              : other == KS ? ks_cycles(kp, cus, ksteps)
                                            : px_cycles(pp, cus, ksteps);
         if (sp.mb && (sched == 4 || sp.cost < price)) {
-            launch_stream_plan(sg, d, sp, cus, ksteps, stream);
+            launch_stream_plan(sg, d, sp, cus, ksteps, false, stream);
             return check_launch("lce_bconv2d_mfma launch");
         }
     }
@@ -1553,17 +1567,38 @@ lce_status lce_quantize_bconv2d_mfma(const lce_bconv2d_desc *desc, const float *
     // 20.6 vs 22.2 us).  The mfma_schedule key restricts the choice to one
     // schedule (the filter-stationary one then up to 72 K steps).
     const int64_t ksteps = (int64_t)d.kh * d.kw * (p.cwe / 2);
-    const int sched = tuning(LCE_TUNE_MFMA_SCHEDULE);   // 0 auto, 1 FS, 2 K split, 3 pixel
-    const bool fs_k = (sched == 0 || sched == 1) && ksteps <= 72 && fs_any_takes(ksteps);
-    const bool ks_k = (sched == 0 && ksteps >= 20) || sched == 2;
+    const int sched = tuning(LCE_TUNE_MFMA_SCHEDULE);   // 0 auto, 1 FS, 2 K split, 3 pixel, 4 streaming
+    const bool fs_k = (sched == 0 || sched == 1 || sched == 4) && ksteps <= 72 && fs_any_takes(ksteps);
+    const bool ks_k = ((sched == 0 || sched == 4) && ksteps >= 20) || sched == 2;
     if (fs_k || ks_k) {
         const int64_t cus = device_simds() / 4;
         const int blocks32 = p.coutp / 32;
         const KsPlan kp = ks_k ? plan_mfma_ks(p, cus, blocks32) : KsPlan{};
-        const bool fs_first =
-            fs_k && (ksteps <= 36 || sched == 1 || !kp.mbw || kp.wgs < cus);
-        if ((fs_first && launch_fs_plan(p, d, plan_mfma_fs(p, cus, blocks32, (int)ksteps), cus, blocks32,
-                                        ksteps, true, stream)) ||
+        const FsPlan fp = fs_k && (ksteps <= 36 || sched == 1 || !kp.mbw || kp.wgs < cus)
+                              ? plan_mfma_fs(p, cus, blocks32, (int)ksteps) : FsPlan{};
+        // the streaming schedule where one of the two takes the layer and its
+        // price is lower, the float regions' included
+        if (sched == 4 || (sched == 0 && !other_keys() && (fp.shape.ks || kp.mbw))) {
+            const lce::MfmaGeom sg = stream_geometry(p);
+            const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32, true);
+            // their float regions: two words per thread in one round of loads,
+            // the others round after round (cycles measured beyond the packed
+            // layer's: 56x56x64 batch 256, 26 words: 73K, batch 16, 2.7: 3.8K;
+            // 28x28x128 batch 64, 4.2: 9.3K; batch 16, 1.9: 1.5K)
+            auto stage = [&](int rows, int width) {
+                const double w = (double)rows * width * p.cw / lce::kMfmaThreads;
+                return 800.0 * std::min(w, 2.0) + 3500.0 * std::max(w - 2.0, 0.0);
+            };
+            const double price =
+                fp.shape.ks ? fs_cycles(fp) + fp.wpc * stage(fp.tile_rows, fp.width)
+                            : ks_cycles(kp, cus, ksteps) +
+                                  (double)((kp.wgs + cus - 1) / cus) * stage(kp.tile_rows, p.pw);
+            if (sp.mb && (sched == 4 || sp.cost < price)) {
+                launch_stream_plan(sg, d, sp, cus, ksteps, true, stream);
+                return check_launch("lce_quantize_bconv2d_mfma launch");
+            }
+        }
+        if (launch_fs_plan(p, d, fp, cus, blocks32, ksteps, true, stream) ||
             (ks_k && launch_ks_plan(p, d, kp, blocks32, true, stream)))
             return check_launch("lce_quantize_bconv2d_mfma launch");
     }

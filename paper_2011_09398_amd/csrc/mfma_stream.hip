@@ -1,4 +1,4 @@
-// Launchers of the streaming matrix-core schedule.
+// Launchers of the streaming matrix-core schedule (packed and float32 input).
 #include "launch.hpp"
 
 namespace lce {
@@ -7,7 +7,9 @@ namespace {
 template <int OUT, int MB, int NB>
 void launch_vec(const StreamParams &p, dim3 grid, size_t lds, hipStream_t s) {
     const dim3 block(kMfmaThreads);
-    if (p.region_vec == 4)
+    if (p.region_vec == 0)
+        hipLaunchKernelGGL((bconv2d_mfma_stream_kernel<OUT, MB, NB, 0>), grid, block, lds, s, p);
+    else if (p.region_vec == 4)
         hipLaunchKernelGGL((bconv2d_mfma_stream_kernel<OUT, MB, NB, 4>), grid, block, lds, s, p);
     else if (p.region_vec == 2)
         hipLaunchKernelGGL((bconv2d_mfma_stream_kernel<OUT, MB, NB, 2>), grid, block, lds, s, p);
