@@ -127,6 +127,8 @@ lce_status lce_bitpack(const float *x, int32_t *out, int64_t rows, int32_t chann
  *              ignored (may be NULL) otherwise
  *   out        see lce_out_type; shape from lce_bconv2d_out_shape
  * Dilation and groups are not part of the operator (always 1).
+ * Filter shapes without a specialized XOR/POPCOUNT instance run on the matrix
+ * cores (below; the same integers) where that is the faster way.
  * All pointers must be 4-byte aligned.
  * Errors: LCE_EINVAL (null desc or required pointer, bad field, no output,
  *         c_out > 2^20, a tensor of 2^31 or more words/elements; with zero

@@ -55,6 +55,8 @@ struct StreamParams : MfmaGeom {
     int32_t row_segs, row_pair;      // 64-lane segments per row; 1: a wave loads two rows at once
     int32_t units;                   // wave loads per region
     int32_t out8;                    // 1: pairs of output words may be stored as 8 bytes
+    uint32_t w_bytes;                // OHWI filters: their size and one filter's
+    int32_t w_row;
     uint32_t pad_fill[4];            // widened +1.0 codes of the last word's padding channels
     FastDiv div_ct, div_tw, div_oh;  // column tiles, tile columns, output rows of an image
     FastDiv div_g, div_segs;         // elements per location, segments per row
@@ -249,8 +251,11 @@ __device__ __forceinline__ void stream_quantize(const StreamParams &p, const Str
 
 // OUT: output kind.  MB x NB blocks of 32 pixels x 32 filters per wave; p.wf of the four waves
 // side by side over filters, the others over pixels.  V: words per region load,
-// 0 for a float32 input.
-template <int OUT, int MB, int NB, int V>
+// 0 for a float32 input.  OHWI: p.wpk is the packed filter tensor itself
+// ([C_out][taps][Cw]); a lane then reads its filter's own words (a 64-byte line
+// serves eight K steps from the L1), and the word past an odd Cw, which belongs
+// to the next tap, is cleared.
+template <int OUT, int MB, int NB, int V, bool OHWI = false>
 __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mfma_stream_kernel(
     StreamParams p) {
     constexpr int RB = 4;                                // packed filters in flight (K steps)
@@ -281,17 +286,42 @@ __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mf
     StreamTile tile = origin(t);
     StreamRegion<V> rch;
     if constexpr (V > 0) stream_load<V>(p, tile, wave, lane, 0, rch);
-    const __amdgpu_buffer_rsrc_t wb = filter_buffer(p, true);
+    const __amdgpu_buffer_rsrc_t wb =
+        OHWI ? buffer_of(p.wpk, p.w_bytes) : filter_buffer(p, true);
     int col[NB];
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
-        col[i] = (half * p.coutp + min(f0 + 32 * i + l32, p.coutp - 1)) * 4;
+    for (int i = 0; i < NB; ++i) {
+        const int co = f0 + 32 * i + l32;
+        col[i] = OHWI ? min(co, p.cout - 1) * p.w_row + half * 4
+                      : (half * p.coutp + min(co, p.coutp - 1)) * 4;
+    }
     const int row8 = p.coutp * 8;
+    // (OHWI, odd Cw: the second half's word of a tap's last pair does not exist)
+    const bool odd = OHWI && (p.cw & 1);
+    const uint32_t half_mask = odd && half ? 0u : ~0u;
     uint32_t bring[RB][NB];
     auto load_b = [&](int s, uint32_t (&d)[NB]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
-            d[i] = __builtin_amdgcn_raw_buffer_load_b32(wb, col[i], s * row8, 0);
+        for (int i = 0; i < NB; ++i) {
+            if constexpr (OHWI) {
+                // (the whole offset in the lane's, which is what the buffer's
+                // size is checked against)
+                const int tap = odd ? (int)fast_div((uint32_t)s, p.div_cwh) : 0;
+                d[i] = __builtin_amdgcn_raw_buffer_load_b32(wb, col[i] + s * 8 - tap * 4, 0, 0);
+            } else {
+                d[i] = __builtin_amdgcn_raw_buffer_load_b32(wb, col[i], s * row8, 0);
+            }
+        }
+    };
+    // the filter word of K step s as it was loaded
+    auto filter_word = [&](uint32_t w, int s) __attribute__((always_inline)) {
+        if constexpr (OHWI) {
+            if (odd) {
+                const int tap = (int)fast_div((uint32_t)s, p.div_cwh);
+                return s - tap * cwh == cwh - 1 ? w & half_mask : w;
+            }
+        }
+        return w;
     };
     uint32_t vmask;
     asm volatile("v_mov_b32 %0, 0x88888888" : "=v"(vmask));
@@ -402,7 +432,8 @@ __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mf
 #pragma unroll
         for (int b = 0; b < MB; ++b) a[b] = *reinterpret_cast<const u32x4 *>(az + a_addr[b]);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) bw[0][i] = widen_word_vm(bring[0][i], kFp4PlusOne, vmask);
+        for (int i = 0; i < NB; ++i)
+            bw[0][i] = widen_word_vm(filter_word(bring[0][i], 0), kFp4PlusOne, vmask);
         // K step s with its filters widened in bc.  Between its products, in
         // pieces short enough to hide behind one: each pixel block's A is read
         // for step s + 1 after the block's last product, the filters of step
@@ -414,6 +445,9 @@ __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mf
             constexpr bool first = decltype(first_c)::value;
             constexpr int RI = decltype(ri_c)::value;
             knext = ko[s + 2];
+            uint32_t wn[NB];                             // the filter words of step s + 1
+#pragma unroll
+            for (int i = 0; i < NB; ++i) wn[i] = filter_word(bring[(RI + 1) % RB][i], s + 1);
             pin();
 #pragma unroll
             for (int b = 0; b < MB; ++b) {
@@ -446,7 +480,7 @@ __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mf
                     for (int e = 0; e < kPer; ++e) {
                         const int j = (b * NB + i) * kPer + e, d = j & 3;
                         bn_[j >> 2][d] =
-                            ((bring[(RI + 1) % RB][j >> 2] << (3 - d)) & vmask) | kFp4PlusOne;
+                            ((wn[j >> 2] << (3 - d)) & vmask) | kFp4PlusOne;
                     }
                     if (b == MB - 1 && i == NB - 1)
                         load_b(s + RB < ksteps ? s + RB : min(RI, ksteps - 1), bring[RI]);

@@ -33,6 +33,10 @@ void launch_mfma_fs_window(const MfmaParams &p, int ks, int s, bool pk, bool qf,
 void launch_mfma_stream(const StreamParams &p, int out_type, int mb, int nb, dim3 grid,
                         size_t lds, hipStream_t stream);
 
+// the same on packed OHWI filters (p.wpk, p.w_bytes, p.w_row; packed input)
+void launch_mfma_stream_ohwi(const StreamParams &p, int out_type, int mb, int nb, dim3 grid,
+                             size_t lds, hipStream_t stream);
+
 // quantize-fused XOR/POPCOUNT convolution (float input, Cw = C_in/32 words
 // per pixel): whether an instance exists, and its launch
 bool has_quant_instance(int cw, int kh, int kw);

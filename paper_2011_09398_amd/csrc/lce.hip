@@ -863,7 +863,7 @@ double fs_cycles(const FsPlan &fp) {
 // 14x14x256 batch 64: 11K, 10.9K; 7x7x512 batch 256: 31K, 30K; 1x1
 // 28x28x256->512 batch 256: 55K, 67K).  mb == 0: no tile fits the LDS.
 StreamPlan plan_stream(const lce::MfmaGeom &p, int64_t cus, int64_t ksteps, int blocks32,
-                       bool qf) {
+                       bool qf, bool ohwi) {
     StreamPlan best;
     const int force_mb = tuning(LCE_TUNE_MFMA_TILE_M), force_bn = tuning(LCE_TUNE_MFMA_TILE_N);
     // {mb, nb, wf}
@@ -925,6 +925,10 @@ StreamPlan plan_stream(const lce::MfmaGeom &p, int64_t cus, int64_t ksteps, int 
         const double rest = 1000.0 + stage_more + 120.0 * s.mb * s.nb;
         s.cost = 5000.0 + (s.nb == 1 ? 1500.0 : 0.0) + stage + 1.35 * products +
                  (n - 1) * (s.per_cu > 1 ? rest + products : rest + 2000.0 + 1.35 * products);
+        // (filters as they are stored: a workgroup's loads of one K step touch
+        // some 256 cache lines, about 700 cycles, which further workgroups on
+        // the CU overlap for the most part)
+        if (ohwi) s.cost += 700.0 * ksteps * (s.per_cu > 1 ? 1.0 + 0.3 * (n - 1) : (double)n);
         if (!best.mb || s.cost < best.cost) best = s;
     }
     return best;
@@ -1032,7 +1036,7 @@ lce::MfmaGeom stream_geometry(const lce::MfmaGeom &g) {
 }
 
 void launch_stream_plan(const lce::MfmaGeom &geom, const lce_bconv2d_desc &d, const StreamPlan &s,
-                        int64_t cus, int64_t ksteps, bool qf, hipStream_t stream) {
+                        int64_t cus, int64_t ksteps, bool qf, bool ohwi, hipStream_t stream) {
     lce::StreamParams p{};
     static_cast<lce::MfmaGeom &>(p) = geom;
     p.tiles = (int)s.tiles;
@@ -1068,7 +1072,63 @@ void launch_stream_plan(const lce::MfmaGeom &geom, const lce_bconv2d_desc &d, co
     const int t = tuning(LCE_TUNE_MFMA_FS_WPC);
     const int64_t slots = std::max<int64_t>(1, cus * (t == 1 || t == 2 ? t : s.per_cu) / s.groups);
     const dim3 grid((unsigned)std::min(slots, s.tiles), (unsigned)s.groups);
-    lce::launch_mfma_stream(p, d.out_type, s.mb, s.nb, grid, s.lds, stream);
+    if (ohwi) {
+        p.w_row = d.kh * d.kw * p.cw * 4;
+        p.w_bytes = (uint32_t)d.c_out * (uint32_t)p.w_row;
+        lce::launch_mfma_stream_ohwi(p, d.out_type, s.mb, s.nb, grid, s.lds, stream);
+    } else {
+        lce::launch_mfma_stream(p, d.out_type, s.mb, s.nb, grid, s.lds, stream);
+    }
+}
+
+// lce_bconv2d, shapes without a specialized XOR/POPCOUNT instance: the
+// streaming matrix-core schedule on the filters as they are stored, where its
+// price is below the generic XOR kernel's (the same integers: K < 2^22 keeps
+// the fp32 accumulation exact).  The generic kernel's price, in cycles: its xor
+// and popcount instructions (5 each on their SIMD) and 0.6 times as long again
+// for staging every im2col row for each 32 filters (3x3/2 200->136 over 45x61
+// batch 64: 100K, 98K measured); a row's words, which arrive one after another,
+// where other waves' instructions do not cover them (5x5x480 8x8 batch 7: 83K,
+// 86K); and 4-byte stores of 64 lanes to 64 cache lines where the 16-byte ones
+// do not serve (1x1 38->228 over 80K pixels: 148K, 185K).
+// us XOR -> here: 1x1 256->512 28x28 batch 256 158 -> 35, 1x1 367->222 19x76
+// batch 143 228 -> 40, 7x7/2 45->223 74x41 batch 74 126 -> 47, 5x5 416->224
+// 9x40 batch 89 251 -> 101, 3x3/2 200->136 45x61 batch 64 49 -> 31.
+// false: not taken, nothing launched.  (Tuning keys of either kernel keep it
+// to XOR.)
+bool launch_generic_on_mfma(const lce_bconv2d_desc &d, const Geometry &g, const int32_t *x_packed,
+                            const int32_t *w_packed, const float *multiplier, const float *bias,
+                            const float *thresholds, const int32_t *flip, void *out,
+                            hipStream_t stream) {
+    const int cw = packed_words(d.c_in);
+    if (has_static(cw, d.kh, d.kw) || tuning(LCE_TUNE_XOR_NB) || tuning(LCE_TUNE_XOR_KS) ||
+        other_keys())
+        return false;
+    int cc, cwe;
+    mfma_chunk(cw, &cc, &cwe);
+    const int64_t ksteps = (int64_t)d.kh * d.kw * (cwe / 2);
+    const int64_t m = (int64_t)d.n * g.oh * g.ow, kwords = (int64_t)d.kh * d.kw * cw;
+    if (64 * ksteps >= 1 << 22 || m > INT32_MAX - lce::kMfmaPixMax ||
+        (int64_t)d.c_out * kwords * 4 >= int64_t(1) << 31)
+        return false;
+    const int64_t cus = device_simds() / 4;
+    const double xors = (double)m * d.c_out * kwords * 2 / 64 * 5 / (4 * cus);
+    const bool wide = d.out_type == LCE_OUT_BITPACKED ||
+                      (d.out_type == LCE_OUT_FLOAT32 && multiplier && bias && d.c_out % 4 == 0 &&
+                       aligned(out, 16));
+    const double price = 4000.0 + 1.6 * xors + std::max(0.0, 200.0 * kwords - 0.8 * xors) +
+                         (wide ? 0.0 : 500.0 * (double)m * d.c_out / 64 / (4 * cus));
+    if (price < 7000.0) return false;                    // (below any streaming plan's)
+    lce::MfmaParams p;
+    if (mfma_params(d, g, x_packed, false, nullptr, multiplier, bias, thresholds, flip, out, &p) !=
+        LCE_OK)
+        return false;
+    p.wpk = reinterpret_cast<const uint32_t *>(w_packed);
+    const lce::MfmaGeom sg = stream_geometry(p);
+    const StreamPlan sp = plan_stream(sg, cus, ksteps, p.coutp / 32, false, true);
+    if (!sp.mb || sp.cost >= price) return false;
+    launch_stream_plan(sg, d, sp, cus, ksteps, false, true, stream);
+    return true;
 }
 
 }  // namespace
@@ -1151,6 +1211,9 @@ lce_status lce_bconv2d(const lce_bconv2d_desc *desc, const int32_t *x_packed,
     p.rs = lce::row_stride(p.slab);
 
     const int filters = d.out_type == LCE_OUT_BITPACKED ? p.cwo * 32 : p.cout;
+    if (launch_generic_on_mfma(d, g, x_packed, w_packed, multiplier, bias, thresholds, flip, out,
+                               stream))
+        return check_launch("lce_bconv2d launch");
     if (has_static(p.cw, p.kh, p.kw) && input_fits_buffer(p)) {
         choose_schedule(p, filters);
     } else {
@@ -1506,12 +1569,12 @@ lce_status lce_bconv2d_mfma(const lce_bconv2d_desc *desc, const int32_t *x_packe
     // (not where a tuning key asks for something of the others)
     if (sched == 4 || (sched == 0 && !other_keys())) {
         const lce::MfmaGeom sg = stream_geometry(p);
-        const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32, false);
+        const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32, false, false);
         const double price = other == FS   ? fs_cycles(fp)
                              : other == KS ? ks_cycles(kp, cus, ksteps)
                                            : px_cycles(pp, cus, ksteps);
         if (sp.mb && (sched == 4 || sp.cost < price)) {
-            launch_stream_plan(sg, d, sp, cus, ksteps, false, stream);
+            launch_stream_plan(sg, d, sp, cus, ksteps, false, false, stream);
             return check_launch("lce_bconv2d_mfma launch");
         }
     }
@@ -1580,7 +1643,7 @@ lce_status lce_quantize_bconv2d_mfma(const lce_bconv2d_desc *desc, const float *
         // price is lower, the float regions' included
         if (sched == 4 || (sched == 0 && !other_keys() && (fp.shape.ks || kp.mbw))) {
             const lce::MfmaGeom sg = stream_geometry(p);
-            const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32, true);
+            const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32, true, false);
             // their float regions: two words per thread in one round of loads,
             // the others round after round (cycles measured beyond the packed
             // layer's: 56x56x64 batch 256, 26 words: 73K, batch 16, 2.7: 3.8K;
@@ -1594,7 +1657,7 @@ lce_status lce_quantize_bconv2d_mfma(const lce_bconv2d_desc *desc, const float *
                             : ks_cycles(kp, cus, ksteps) +
                                   (double)((kp.wgs + cus - 1) / cus) * stage(kp.tile_rows, p.pw);
             if (sp.mb && (sched == 4 || sp.cost < price)) {
-                launch_stream_plan(sg, d, sp, cus, ksteps, true, stream);
+                launch_stream_plan(sg, d, sp, cus, ksteps, true, false, stream);
                 return check_launch("lce_quantize_bconv2d_mfma launch");
             }
         }
