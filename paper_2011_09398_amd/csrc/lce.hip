@@ -846,9 +846,9 @@ struct StreamPlan {
 
 // Cycles of a filter-stationary plan: a set-up, then its pixel blocks at 50
 // cycles a product, plus the exchange where waves share a filter block
-// (28x28x128 batch 64: 11.8K predicted, 10.6K measured; batch 256: 28K, 26K;
-// 14x14x256 batch 64: 14K, 13K; 56x56x64->128/s2 batch 64: 9.1K, 8.6K;
-// 56x56x64->64 batch 64: 19.7K, 23K).
+// (28x28x128 batch 64: 11.3K predicted, 10.6K measured; batch 256: 28K, 26K;
+// 14x14x256 batch 64: 13.5K, 13K; 56x56x64->128/s2 batch 64: 8.6K, 8.6K;
+// 56x56x64->64 batch 64: 19.2K, 23K).
 double fs_cycles(const FsPlan &fp) {
     const int nb = (fp.pixels + 31) / 32;
     return 5000.0 + (double)nb * fp.wpc * (50.0 * fp.shape.ks + (fp.shape.s > 1 ? 320.0 : 0.0));
@@ -859,9 +859,10 @@ double fs_cycles(const FsPlan &fp) {
 // cycles (nothing else to run meanwhile); each further one on the same CU its
 // products at the full rate, and the staging and output that do not overlap
 // them (at 2.1 GHz, measured less the launch: 56x56x64->64 batch 256, tiles of
-// two blocks per wave: 45K, predicted 41K; 28x28x128 batch 256: 30K, 36K;
-// 14x14x256 batch 64: 11K, 10.9K; 7x7x512 batch 256: 31K, 30K; 1x1
-// 28x28x256->512 batch 256: 55K, 67K).  mb == 0: no tile fits the LDS.
+// two blocks per wave: 45K, predicted 55K; 28x28x128 batch 256: 30K, 40K;
+// 14x14x256 batch 64: 11K, 12K; 7x7x512 batch 256: 31K, 33K; 1x1
+// 28x28x256->512 batch 256: 57K, 58K).  It errs high where the others are
+// close, so that they keep the layer.  mb == 0: no tile fits the LDS.
 StreamPlan plan_stream(const lce::MfmaGeom &p, int64_t cus, int64_t ksteps, int blocks32,
                        bool qf, bool ohwi) {
     StreamPlan best;
