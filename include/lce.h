@@ -113,6 +113,9 @@ lce_status lce_bitpack(const float *x, int32_t *out, int64_t rows, int32_t chann
  * output transform.
  *   x_packed   int32 [N][H][W][ceil(C_in/32)]          (device)
  *   w_packed   int32 [C_out][KH][KW][ceil(C_in/32)]    (device)
+ *              The bits of a last word past C_in must be 0 in both, as
+ *              lce_bitpack and a bitpacked output write them: the XOR counts
+ *              every bit of a word.
  *   multiplier float [C_out] or NULL (= 1.0)   used by FLOAT32 output only
  *   bias       float [C_out] or NULL (= 0.0)   used by FLOAT32 output only
  *   thresholds float [C_out], required by BITPACKED output only
@@ -240,7 +243,7 @@ lce_status lce_bconv2d_mfma_weights(const lce_bconv2d_desc *desc, const int32_t 
 /* LceBConv2d on the matrix cores: arguments, output and every rounding as
  * lce_bconv2d (multiplier/bias for FLOAT32, thresholds and optional flip for
  * BITPACKED), with the widened filters in place of w_packed and either
- * pad_value (no correction table).
+ * pad_value (no correction table).  Bits of x_packed past C_in are ignored.
  * The work is split by shape between four schedules: filter-stationary
  * (each wave keeps its filters in registers and runs through about one
  * CU's share of pixel blocks; by default up to 36 K steps of 64

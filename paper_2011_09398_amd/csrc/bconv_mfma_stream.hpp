@@ -23,9 +23,11 @@
 //   * A tile is whole output rows where those fill it, else 32*k columns of
 //     several rows, so that wide images stage 3 x 34 locations and not whole
 //     rows, and the 32 pixels of a block are always consecutive in memory.
-//   * Channels past C_in: their bits are 0 in both operands, widen to +1.0 on
-//     both sides and add the same to every dot; that sum is taken out at the
-//     end (or of the threshold).  So the packed filters serve every C_in.
+//   * Channels past C_in: their bits are 0 in both operands (masked off the
+//     input's last word, where the widened filters of the other schedules hold
+//     0.0), widen to +1.0 on both sides and add the same to every dot; that sum
+//     is taken out at the end (or of the threshold).  So the packed filters
+//     serve every C_in.
 //
 // Measured (us; the schedule that took the layer before, and this one):
 // 56x56x64->64 batch 256 44.9 -> 21.5, 14x14x256 batch 256 42 -> 15.8,
@@ -58,6 +60,7 @@ struct StreamParams : MfmaGeom {
     uint32_t w_bytes;                // OHWI filters: their size and one filter's
     int32_t w_row;
     uint32_t pad_fill[4];            // widened +1.0 codes of the last word's padding channels
+    uint32_t tail;                   // bits of an input location's last word that are channels
     FastDiv div_ct, div_tw, div_oh;  // column tiles, tile columns, output rows of an image
     FastDiv div_g, div_segs;         // elements per location, segments per row
 };
@@ -155,15 +158,18 @@ __device__ __forceinline__ void stream_load(const StreamParams &p, const StreamT
 
 // Widen a wave's loads into the A tile: +1.0/-1.0 from the bits, 0.0 at
 // padding locations under zero padding, where the padding channels of the
-// last word stay +1.0 (they add the same to every dot).
-template <int V>
+// last word stay +1.0 (they add the same to every dot).  TAIL: the input's bits
+// past C_in are cleared.
+template <int V, bool TAIL>
 __device__ __forceinline__ void stream_widen(const StreamParams &p, const StreamRegion<V> &ch,
                                              u32x4 *atile, int wave, int lane, int u0) {
     int c, g, at;
+    uint32_t tail;
     bool ok;
     auto place = [&](int seg) __attribute__((always_inline)) {
         stream_lane<V>(p, lane, seg, c, g, ok);
         at = V * g * p.plane + c;
+        tail = TAIL && V * g + V == p.cw ? p.tail : ~0u;
     };
     if (p.row_segs == 1) place(0);
 #pragma unroll
@@ -182,7 +188,8 @@ __device__ __forceinline__ void stream_widen(const StreamParams &p, const Stream
             const uint32_t fill = zero ? 0u : kFp4PlusOne;
 #pragma unroll
             for (int k = 0; k < V; ++k) {
-                u32x4 o = widen_word(ch.w[V * u + k], fill);
+                const uint32_t w = k == V - 1 ? ch.w[V * u + k] & tail : ch.w[V * u + k];
+                u32x4 o = widen_word(w, fill);
                 if (k == V - 1 && zero && V * g + V == p.cw)
                     o = u32x4{p.pad_fill[0], p.pad_fill[1], p.pad_fill[2], p.pad_fill[3]};
                 atile[at + r * p.pw + k * p.plane] = o;
@@ -254,7 +261,8 @@ __device__ __forceinline__ void stream_quantize(const StreamParams &p, const Str
 // 0 for a float32 input.  OHWI: p.wpk is the packed filter tensor itself
 // ([C_out][taps][Cw]); a lane then reads its filter's own words (a 64-byte line
 // serves eight K steps from the L1), and the word past an odd Cw, which belongs
-// to the next tap, is cleared.
+// to the next tap, is cleared; every bit of an input word counts, as in the XOR
+// kernels (the mask there measured 31.0 -> 32.8 us on 3x3/2 200->136).
 template <int OUT, int MB, int NB, int V, bool OHWI = false>
 __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mfma_stream_kernel(
     StreamParams p) {
@@ -389,11 +397,11 @@ __global__ __launch_bounds__(kMfmaThreads, MB * NB <= 4 ? 3 : 2) void bconv2d_mf
         if constexpr (V == 0) {
             stream_quantize(p, tile, atile, wavev, lanev);
         } else {
-            stream_widen<V>(p, rch, atile, wavev, lanev, 0);
+            stream_widen<V, !OHWI>(p, rch, atile, wavev, lanev, 0);
             for (int u0 = stream_reg_u(V); wavev + 4 * u0 < p.units; u0 += stream_reg_u(V)) {
                 StreamRegion<V> ch;
                 stream_load<V>(p, tile, wavev, lanev, u0, ch);
-                stream_widen<V>(p, ch, atile, wavev, lanev, u0);
+                stream_widen<V, !OHWI>(p, ch, atile, wavev, lanev, u0);
             }
         }
         // windows below an image boundary lie further down

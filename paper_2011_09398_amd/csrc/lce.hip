@@ -1054,6 +1054,7 @@ void launch_stream_plan(const lce::MfmaGeom &geom, const lce_bconv2d_desc &d, co
             if (d.c_in % 32 && c >= d.c_in % 32) f |= 2u << (c / 4 * 4);
         p.pad_fill[w] = f;
     }
+    p.tail = d.c_in % 32 == 0 ? ~0u : (1u << d.c_in % 32) - 1u;
     p.tile_rows = s.tile_rows;
     p.pw = s.width;
     p.plane = s.plane;

@@ -140,3 +140,20 @@ def test_stream_is_chosen_and_agrees(stream):
             outs.append(stream.bconv2d_mfma(xp, wf, c_in, c_out, k, out_type="int32"))
         for o in outs[1:]:
             assert torch.equal(outs[0], o)
+
+
+@pytest.mark.parametrize("out", ["int32", "bitpacked"])
+@pytest.mark.parametrize("pad_value", ["one", "zero"])
+@pytest.mark.parametrize("c_in", [45, 70, 100])
+@pytest.mark.parametrize("sched", ["auto", "fs", "ksplit", "pixel", "stream"])
+def test_input_bits_past_the_channels_count_nothing(stream, sched, c_in, pad_value, out):
+    """The widened filters hold 0.0 there, so bits of x_packed past C_in do not
+    reach any dot, whichever schedule runs (1, 2 and 4 words per region load)."""
+    stream.set_tuning(mfma_schedule=sched)
+    layer = Layer("p", 2, 9, 13, c_in, 64, out=out)
+    inp = make_layer_inputs(layer, 35, 90, 4)
+    words = stream.bitpack(dev(inp.x_float))
+    words[..., -1] |= -1 << (c_in % 32)
+    ref = oracle_run(layer, inp, oracle_signs(inp), 0 if pad_value == "zero" else 1)
+    got = sync_np(mfma_run(layer, inp, pad_value=pad_value, x_packed=words))
+    assert_match(layer, got, ref, f"{sched} {c_in} {pad_value}")
