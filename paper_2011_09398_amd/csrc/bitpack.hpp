@@ -54,6 +54,29 @@ __global__ __launch_bounds__(kBitpackThreads) void bitpack32_kernel(
     }
 }
 
+// Rows of one word and few channels: one thread per row, whose few loads lie in
+// the lines that its neighbours' loads touch, with no barrier.
+__global__ __launch_bounds__(kBitpackThreads) void bitpack_short_kernel(
+    const float *__restrict__ x, uint32_t *__restrict__ out, int64_t rows, int channels) {
+    const int64_t stride = (int64_t)gridDim.x * kBitpackThreads;
+    for (int64_t r = (int64_t)blockIdx.x * kBitpackThreads + threadIdx.x; r < rows; r += stride) {
+        const float *src = x + r * channels;
+        uint32_t word = 0;
+        for (int b = 0; b < channels; ++b) word |= (uint32_t)(src[b] < 0.0f) << b;
+        out[r] = word;
+    }
+}
+
+// Whether bitpack_short_kernel packs these rows faster than the general path
+// (us short, general; rows x channels: 4096x7 2.4, 2.6; 65536x3 2.4, 3.3;
+// 2000000x3 6.9, 8.3; 500000x6 4.4, 5.1, but 1000000x6 7.3, 6.0; 65536x12 3.0,
+// 3.3, but 4096x12 2.8, 2.6 and 130000x8 3.7, 3.4).
+inline bool bitpack_short(int64_t rows, int channels) {
+    const int64_t floats = rows * channels;
+    return channels <= 3 || (channels <= 7 && floats <= 3 << 20) ||
+           (channels <= 12 && rows > 40000 && rows <= 100000);
+}
+
 // General path: any channel count and 4-byte alignment.  A row's words start
 // anywhere in the float stream, so the signs are first packed as they lie in
 // memory (16-byte loads, the fast path's nibbles) into LDS, and each output
@@ -61,9 +84,12 @@ __global__ __launch_bounds__(kBitpackThreads) void bitpack32_kernel(
 // wave and instruction.  A workgroup takes `chunk` consecutive output words at
 // a time, which cover at most 32*chunk consecutive floats.  (One thread per
 // word, walking its own 32 floats, read 64 cache lines per instruction: 64
-// images of 56x56x72, 60 MB, 124 us; this 16 us, 3.8 TB/s.)
+// images of 56x56x72, 60 MB, 124 us; this 12 us, 5.0 TB/s.)
+// U: 16-byte loads in flight per thread: 2 where a pass has no more (64 rows of
+// 33 channels: 2.3 us against 2.9 with 8, most of them nothing), else 8.
 constexpr int kBitpackChunk = 1024;   // words per workgroup pass, at most
 
+template <int U>
 __global__ __launch_bounds__(kBitpackThreads) void bitpack_generic_kernel(
     const float *__restrict__ x, uint32_t *__restrict__ out, int64_t rows, int channels, int chunk,
     FastDiv div_cw) {
@@ -86,11 +112,10 @@ __global__ __launch_bounds__(kBitpackThreads) void bitpack_generic_kernel(
         const int64_t end = (r0 + rl) * channels + min((int64_t)channels, (int64_t)jl * 32 + 32);
         const int64_t q0 = (first + skew) >> 2;                  // 16-byte units
         const int nq = (int)(((end + skew + 3) >> 2) - q0);
-        constexpr int kU = 8;                                    // loads in flight per thread
-        for (int b = 0; b < nq; b += kU * kBitpackThreads) {
-            float4 v[kU];
+        for (int b = 0; b < nq; b += U * kBitpackThreads) {
+            float4 v[U];
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const int i = b + u * kBitpackThreads + tid;
                 const int64_t f = ((q0 + i) << 2) - skew;        // the unit's first float
                 v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -106,7 +131,7 @@ __global__ __launch_bounds__(kBitpackThreads) void bitpack_generic_kernel(
                 }
             }
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const int i = b + u * kBitpackThreads + tid;
                 uint32_t s = ((uint32_t)(v[u].x < 0.0f) | ((uint32_t)(v[u].y < 0.0f) << 1) |
                               ((uint32_t)(v[u].z < 0.0f) << 2) | ((uint32_t)(v[u].w < 0.0f) << 3))

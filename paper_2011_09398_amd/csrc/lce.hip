@@ -1171,16 +1171,28 @@ lce_status lce_bitpack(const float *x, int32_t *out, int64_t rows, int32_t chann
                            dim3(lce::kBitpackThreads), 0, stream,
                            reinterpret_cast<const float4 *>(x), reinterpret_cast<uint32_t *>(out),
                            nwords);
+    } else if (lce::bitpack_short(rows, channels)) {
+        const int64_t blocks =
+            std::min<int64_t>((rows + lce::kBitpackThreads - 1) / lce::kBitpackThreads, 256 * 32);
+        hipLaunchKernelGGL(lce::bitpack_short_kernel, dim3((unsigned)blocks),
+                           dim3(lce::kBitpackThreads), 0, stream, x,
+                           reinterpret_cast<uint32_t *>(out), rows, (int)channels);
     } else {
         // words per workgroup pass: enough workgroups for the CUs (four each),
         // then as many words as the LDS string holds
         int64_t chunk = (nwords + 1023) / 1024;
         chunk = std::min<int64_t>(std::max<int64_t>((chunk + 63) / 64 * 64, 64), lce::kBitpackChunk);
         const int64_t blocks = std::min<int64_t>((nwords + chunk - 1) / chunk, 256 * 16);
-        hipLaunchKernelGGL(lce::bitpack_generic_kernel, dim3((unsigned)blocks),
-                           dim3(lce::kBitpackThreads), 0, stream, x,
-                           reinterpret_cast<uint32_t *>(out), rows, (int)channels, (int)chunk,
-                           lce::make_fastdiv((uint32_t)cw));
+        const dim3 grid((unsigned)blocks), block(lce::kBitpackThreads);
+        uint32_t *words = reinterpret_cast<uint32_t *>(out);
+        const lce::FastDiv div = lce::make_fastdiv((uint32_t)cw);
+        // (loads of a pass: its rows' floats, and what its ends cut)
+        if ((chunk / cw + 1) * channels / 4 <= 2 * lce::kBitpackThreads)
+            hipLaunchKernelGGL(lce::bitpack_generic_kernel<2>, grid, block, 0, stream, x, words,
+                               rows, (int)channels, (int)chunk, div);
+        else
+            hipLaunchKernelGGL(lce::bitpack_generic_kernel<8>, grid, block, 0, stream, x, words,
+                               rows, (int)channels, (int)chunk, div);
     }
     return check_launch("lce_bitpack launch");
 }
@@ -1455,18 +1467,33 @@ lce_status lce_dequantize(const int32_t *x_packed, float *out, int64_t rows, int
                            reinterpret_cast<const uint32_t *>(x_packed),
                            reinterpret_cast<float4 *>(out), n4);
     } else {
-        const int64_t blocks =
-            std::min<int64_t>((count + lce::kDequantChunk - 1) / lce::kDequantChunk, 256 * 64);
-        const lce::FastDiv div = lce::make_fastdiv((uint32_t)channels);
+        // us one float per thread, chunks: 72 channels, aligned, 6 M
+        // floats 7.0, 7.7, 8 M 9.7, 9.3, 20 M 19.6, 16.7; 17 channels (rows cut the
+        // four floats), 12 M 13.3, 13.7, 20 M 19.5, 19.0, 30 M 27.6, 24.9;
+        // unaligned, 12 M 13.4, 15.6, 30 M 28.3, 29.1, 87 M 164, 123.  Four
+        // floats that never cross a row take one pass per workgroup: 50 M 34.4
+        // against 33.9 in four, 200 M 204 against 228.
+        const int64_t M = 1 << 20;
         const int cw = packed_words(channels);
-        if (aligned(out, 16))
-            hipLaunchKernelGGL(lce::dequantize_generic_kernel<4>, dim3((unsigned)blocks),
-                               dim3(lce::kPoolThreads), 0, stream,
-                               reinterpret_cast<const uint32_t *>(x_packed), out, count, cw, div);
+        const lce::FastDiv div = lce::make_fastdiv((uint32_t)channels);
+        const uint32_t *words = reinterpret_cast<const uint32_t *>(x_packed);
+        const dim3 block(lce::kPoolThreads);
+        auto grid = [&](int64_t per_block, int64_t most) {
+            return dim3((unsigned)std::min<int64_t>((count + per_block - 1) / per_block, most));
+        };
+        const bool vec = aligned(out, 16), whole = channels % 4 == 0;
+        if (count < (!vec || channels <= 2 ? 32 : whole ? 7 : 14) * M)
+            hipLaunchKernelGGL(lce::dequantize_float_kernel, grid(lce::kPoolThreads, 256 * 16),
+                               block, 0, stream, words, out, (uint32_t)count, cw, div);
+        else if (vec && whole)
+            hipLaunchKernelGGL((lce::dequantize_generic_kernel<4, 1024>), grid(1024, 4 * M), block,
+                               0, stream, words, out, count, cw, div);
+        else if (vec)
+            hipLaunchKernelGGL((lce::dequantize_generic_kernel<4, 4096>), grid(4096, 256 * 64),
+                               block, 0, stream, words, out, count, cw, div);
         else
-            hipLaunchKernelGGL(lce::dequantize_generic_kernel<1>, dim3((unsigned)blocks),
-                               dim3(lce::kPoolThreads), 0, stream,
-                               reinterpret_cast<const uint32_t *>(x_packed), out, count, cw, div);
+            hipLaunchKernelGGL((lce::dequantize_generic_kernel<1, 4096>), grid(4096, 256 * 64),
+                               block, 0, stream, words, out, count, cw, div);
     }
     return check_launch("lce_dequantize launch");
 }

@@ -12,8 +12,8 @@
 //                  bit 0 -> +1.0f, built directly as the IEEE pattern
 //                  0x3F800000 | bit << 31.
 //
-// Both are memory-bound: one thread per output word vector (pooling) or per
-// output float4 (dequantize), consecutive threads on consecutive addresses,
+// Both are memory-bound: one thread per output word vector (pooling), output
+// float or output float4 (dequantize), consecutive threads on consecutive addresses,
 // grid-stride loops over a grid of at most a few workgroups per CU.
 #pragma once
 
@@ -114,32 +114,41 @@ __global__ __launch_bounds__(kPoolThreads) void dequantize32_kernel(const uint32
     }
 }
 
-// Dequantize, any channel count: VEC consecutive output floats per thread (4,
-// 16-byte stores, where out is 16-byte aligned; else 1), which may lie in
-// several words and rows.  A workgroup takes kDequantChunk consecutive floats
-// at a time, so that the row of each is a 32-bit division from the first one's.
-// (One float per thread with a 64-bit division: 64 images of 56x56x72, 60 MB,
-// 18.8 us; this 12 us.)
-constexpr int kDequantChunk = 4096;
+// Dequantize, any channel count: one output float per thread, its row a 32-bit
+// division away (3 M floats of 72 channels 5.1 us; with a 64-bit division 6.2).
+__global__ __launch_bounds__(kPoolThreads) void dequantize_float_kernel(
+    const uint32_t *__restrict__ x, float *__restrict__ out, uint32_t count, int cw,
+    FastDiv div_c) {
+    const uint32_t stride = gridDim.x * kPoolThreads;
+    for (uint32_t i = blockIdx.x * kPoolThreads + threadIdx.x; i < count; i += stride) {
+        const uint32_t r = fast_div(i, div_c), c = i - r * div_c.d;
+        const uint32_t w = x[(size_t)r * cw + (c >> 5)] >> (c & 31);
+        out[i] = __uint_as_float(0x3F800000u | w << 31);
+    }
+}
 
-template <int VEC>
+// The same for large tensors: VEC consecutive output floats per thread (4,
+// 16-byte stores, where out is 16-byte aligned; else 1), which may lie in
+// several words and rows.  A workgroup takes CHUNK consecutive floats at a
+// time, so that the row of each is a 32-bit division from the first one's, and
+// the workgroups in flight write one run of memory.
+template <int VEC, int CHUNK>
 __global__ __launch_bounds__(kPoolThreads) void dequantize_generic_kernel(
     const uint32_t *__restrict__ x, float *__restrict__ out, int64_t count, int cw,
     FastDiv div_c) {
     const int channels = (int)div_c.d;
-    for (int64_t f0 = (int64_t)blockIdx.x * kDequantChunk; f0 < count;
-         f0 += (int64_t)gridDim.x * kDequantChunk) {
+    for (int64_t f0 = (int64_t)blockIdx.x * CHUNK; f0 < count; f0 += (int64_t)gridDim.x * CHUNK) {
         const int64_t r0 = f0 / channels;
         const uint32_t c0 = (uint32_t)(f0 - r0 * channels);
         const uint32_t *xr = x + r0 * cw;
-        const int n = (int)min((int64_t)kDequantChunk, count - f0);
+        const int n = (int)min((int64_t)CHUNK, count - f0);
 #pragma unroll
-        for (int u = 0; u < kDequantChunk / (VEC * kPoolThreads); ++u) {
+        for (int u = 0; u < CHUNK / (VEC * kPoolThreads); ++u) {
             const int i = (u * kPoolThreads + (int)threadIdx.x) * VEC;
             if (i >= n) break;
             // (at most one row end where rows are longer than the chunk; the sum
             // may pass the division's 2^31 only there)
-            uint32_t r = channels >= kDequantChunk ? (c0 + i >= (uint32_t)channels)
+            uint32_t r = channels >= CHUNK ? (c0 + i >= (uint32_t)channels)
                                                    : fast_div(c0 + i, div_c);
             uint32_t c = c0 + i - r * channels;
             uint32_t v[VEC];

@@ -12,8 +12,17 @@ SHAPES = [(1, 1), (5, 1), (4097, 3), (1, 31), (3000, 33), (777, 72), (40, 100), 
           (9, 4095), (2, 4097), (65, 64), (70001, 7), (1, 65537)]
 
 
-@pytest.mark.parametrize("offset", [0, 1, 2, 3])
-@pytest.mark.parametrize("rows,channels", SHAPES)
+# on either side of what picks a kernel: few channels and rows (bitpack), floats
+# and channels (dequantize; rows of whole four floats, rows that cut them, rows
+# longer than a workgroup's pass, two channels)
+LARGE = [(40001, 12), (100001, 12), (449390, 7), (449389, 7), (1500000, 3), (101945, 72),
+         (101944, 72), (863534, 17), (863533, 17), (2, 3670016), (3, 4900003), (2000001, 17),
+         (16777217, 2)]
+
+
+@pytest.mark.parametrize("rows,channels,offset",
+                         [(r, c, o) for r, c in SHAPES for o in range(4)] +
+                         [(r, c, o) for r, c in LARGE for o in (0, 1)])
 def test_codec_edges(rows, channels, offset):
     import torch
     if not torch.cuda.is_available():
