@@ -272,6 +272,8 @@ __global__ __launch_bounds__(kMfmaThreads) void bconv2d_mfma_kernel(MfmaParams p
     constexpr int kStage = CC * BN;                                   // u32x4 per B stage
     constexpr int kDmaPerStage = kStage / 64;                         // 1 KB instructions
     constexpr int kDmaPerWave = (kDmaPerStage + 3) / 4;
+    static_assert(kDmaPerStage < 4 || kDmaPerStage % 4 == 0,
+                  "waves issue kDmaPerWave instructions a stage, or one or none");
     // B stages: four separate arrays, so that the compiler can tell the
     // stage being read from the ones being written by DMA
     __shared__ __attribute__((aligned(16))) u32x4 bslot0[kStage];
@@ -463,14 +465,19 @@ __global__ __launch_bounds__(kMfmaThreads) void bconv2d_mfma_kernel(MfmaParams p
     };
 
     // One stage: this wave's DMA of stage s has landed once at most the two
-    // later stages' instructions are outstanding; after the barrier every
-    // wave's has, and the slot of stage s-1 is free for stage s+3.  At a
-    // chunk's first tap the chunk is widened first (the barrier before it
-    // also retires every wave's reads of the previous chunk).
+    // later stages' instructions are outstanding (where a stage has fewer
+    // instructions than there are waves, some waves issue none: their region
+    // loads are then the last ones, and nothing may be outstanding); after the
+    // barrier every wave's has, and the slot of stage s-1 is free for stage
+    // s+3.  At a chunk's first tap the chunk is widened first (the barrier
+    // before it also retires every wave's reads of the previous chunk).
     auto stage = [&](int s, const u32x4 *cur, u32x4 *refill, OpsA &oa, OpsB &ob, OpsA &pa,
                      OpsB &pb, bool first) __attribute__((always_inline)) {
         const int ch = s / taps, t = s - ch * taps;
-        wait_vmcnt<2 * kDmaPerWave>();
+        if (kDmaPerStage < 4 && wave >= kDmaPerStage)
+            wait_vmcnt<0>();
+        else
+            wait_vmcnt<2 * kDmaPerWave>();
         if (t == 0) {
             const int z = lds_barrier();     // the A tile is free (and the region landed)
             widen_chunk(ch * CC, z);
