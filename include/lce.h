@@ -376,6 +376,12 @@ int32_t lce_get_tuning(int32_t key);
 /* Message describing the last error on the calling thread ("" if none). */
 const char *lce_last_error(void);
 
+/* What the calling thread's last convolution call that got as far as a launch
+ * ran, for tests and tuning: "xor", "xor-generic", "xor-quantize",
+ * "filter-stationary", "k-split", "pixel-split", "streaming" or
+ * "streaming-stored" (lce_bconv2d on the matrix cores); "" before any. */
+const char *lce_last_schedule(void);
+
 #ifdef __cplusplus
 }
 #endif

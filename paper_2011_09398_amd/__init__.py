@@ -38,7 +38,7 @@ EXPORTS = ("lce_packed_words", "lce_bconv2d_out_shape", "lce_bitpack", "lce_bcon
            "lce_dequantize", "lce_bconv2d_mfma_weights_size", "lce_bconv2d_mfma_weights",
            "lce_bconv2d_mfma", "lce_quantize_bconv2d", "lce_quantize_bconv2d_mfma",
            "lce_set_tuning", "lce_get_tuning",
-           "lce_last_error")
+           "lce_last_error", "lce_last_schedule")
 
 # lce_tuning_key values, by the names tuning() takes.
 TUNING_KEYS = {"xor_nb": 0, "xor_ks": 1, "mfma_schedule": 2, "mfma_fs_ks": 3, "mfma_fs_s": 4,
@@ -117,12 +117,19 @@ def lib() -> ctypes.CDLL:
         L.lce_get_tuning.restype = i32
         L.lce_last_error.argtypes = []
         L.lce_last_error.restype = ctypes.c_char_p
+        L.lce_last_schedule.argtypes = []
+        L.lce_last_schedule.restype = ctypes.c_char_p
         _lib = L
     return _lib
 
 
 def last_error() -> str:
     return lib().lce_last_error().decode()
+
+
+def last_schedule() -> str:
+    """The schedule of this thread's last convolution (lce_last_schedule)."""
+    return lib().lce_last_schedule().decode()
 
 
 def _check(status: int) -> None:

@@ -97,6 +97,7 @@ __global__ __launch_bounds__(256) void mfma_expand_weights_kernel(const uint32_t
 namespace {
 
 thread_local std::string g_last_error;
+thread_local const char *g_last_schedule = "";   // of the last convolution launched
 
 lce_status fail(lce_status st, const char *fmt, ...) {
     char buf[512];
@@ -758,6 +759,7 @@ lce_status mfma_params(const lce_bconv2d_desc &d, const Geometry &g, const void 
 bool launch_fs_plan(lce::MfmaParams &p, const lce_bconv2d_desc &d, const FsPlan &fp, int64_t cus,
                     int blocks32, int64_t ksteps, bool qf, hipStream_t stream) {
     if (!fp.shape.ks) return false;
+    g_last_schedule = "filter-stationary";
     p.tile_rows = fp.tile_rows;
     p.fs_pixels = fp.pixels;
     p.fs_thr_off = (int32_t)(mfma_fs_thr_offset(fp.shape) / 4);
@@ -823,6 +825,7 @@ KsPlan plan_mfma_ks(const lce::MfmaParams &p, int64_t cus, int blocks32) {
 bool launch_ks_plan(lce::MfmaParams &p, const lce_bconv2d_desc &d, const KsPlan &kp, int blocks32,
                     bool qf, hipStream_t stream) {
     if (!kp.mbw) return false;
+    g_last_schedule = "k-split";
     p.tile_rows = kp.tile_rows;
     p.div_plane = lce::make_fastdiv((uint32_t)(kp.tile_rows * p.pw));
     const dim3 grid((unsigned)(((int64_t)p.m + 32 * kp.mbw - 1) / (32 * kp.mbw)),
@@ -849,7 +852,7 @@ struct StreamPlan {
 // (28x28x128 batch 64: 11.3K predicted, 10.6K measured; batch 256: 28K, 26K;
 // 14x14x256 batch 64: 13.5K, 13K; 56x56x64->128/s2 batch 64: 8.6K, 8.6K;
 // 56x56x64->64 batch 64: 19.2K, 23K).
-double fs_cycles(const FsPlan &fp) {
+double fs_count(const FsPlan &fp) {
     const int nb = (fp.pixels + 31) / 32;
     return 5000.0 + (double)nb * fp.wpc * (50.0 * fp.shape.ks + (fp.shape.s > 1 ? 320.0 : 0.0));
 }
@@ -938,7 +941,7 @@ StreamPlan plan_stream(const lce::MfmaGeom &p, int64_t cus, int64_t ksteps, int 
 // Cycles of a K-split plan: a workgroup is alone on its CU where its LDS leaves
 // no room for another (7x7x512 batch 256, 5x5x256 64x64 batch 32: 17K and 20K a
 // workgroup measured), else its set-up hides behind another's products.
-double ks_cycles(const KsPlan &kp, int64_t cus, int64_t ksteps) {
+double ks_count(const KsPlan &kp, int64_t cus, int64_t ksteps) {
     const double products = 32.0 * kp.mbw * kp.nblk * ((ksteps + 3) / 4);
     const int64_t n = (kp.wgs + cus - 1) / cus;
     const bool alone = 2 * kp.lds > (size_t)device_max_lds();
@@ -992,6 +995,7 @@ PxPlan plan_mfma_pixel(const lce::MfmaParams &p, int64_t cus, int blocks32, int 
 
 void launch_px_plan(lce::MfmaParams &p, const lce_bconv2d_desc &d, const PxPlan &b, int blocks32,
                     int cc, hipStream_t stream) {
+    g_last_schedule = "pixel-split";
     p.tile_rows = b.tile_rows;
     p.div_plane = lce::make_fastdiv((uint32_t)(b.tile_rows * p.pw));
     const int bm = 128 * b.mb;
@@ -1005,11 +1009,156 @@ void launch_px_plan(lce::MfmaParams &p, const lce_bconv2d_desc &d, const PxPlan 
 // measured); with others to overlap it the products, or the staging and the
 // output, count (5x5x64 91x52 batch 79: 60K, 57K; 1x1 28x28x256->512 batch 256:
 // 117K, 118K; 1x1 160->256 over 103K pixels: 35K, 36K).
-double px_cycles(const PxPlan &b, int64_t cus, int64_t ksteps) {
+double px_count(const PxPlan &b, int64_t cus, int64_t ksteps) {
     const double products = 32.0 * b.mb * b.nblk * ksteps;
     const int64_t n = (b.wgs + cus - 1) / cus;
     return 4500.0 + 250.0 * ksteps + 3.2 * products +
            (n - 1) * std::max(1500.0 + 2.0 * products, 9000.0 * b.mb * b.nblk / 8);
+}
+
+// The counts above come from single layers and are off by up to a half on
+// others (a wave's loads of the region cost alike however many of its lanes are
+// in use; stores of 4-byte outputs), so a schedule that they put before the
+// standing one (filter-stationary, else by K steps; XOR) replaces it only where
+// the prices below agree: cycles at 2.1 GHz of the whole launch, some 4200 of
+// them the launch itself, each linear in what its kernel does on the busiest CU
+// (rounds of workgroups, products, loads and widening of the region, output
+// blocks) and in the bytes written and, from float32, read.  Their coefficients
+// are fitted to the times of every schedule on 17,000 random layers (1x1 to
+// 7x7, strides 1 to 3, 8 to 1024 channels, 0.2 to 200 GOP, the three outputs);
+// on 4000 others the time lies between 0.89 and 1.17 of the price in nine
+// layers of ten, for each schedule.  By the counts alone 134 of 3333 layers ran
+// more than 5% slower than on the standing schedule, the worst 3.8 times
+// (float32 input: 66 of 1771, 1.7 times; stored filters: 10 of 1896, 1.4 times);
+// with both 36, 14 and 4, 1.3 times.
+struct LayerCost {
+    bool floats;          // 4-byte outputs
+    double edge;          // a block's further stores where filters do not fill lines
+    double out, in;       // bytes written, float32 bytes read, in 2500ths
+    int cw;
+};
+
+LayerCost layer_cost(const lce::MfmaGeom &p, int out_type, bool qf) {
+    LayerCost c;
+    c.floats = out_type != LCE_OUT_BITPACKED;
+    c.edge = c.floats && p.cout % 32 ? 1.0 : 0.0;
+    c.out = 4.0 * p.m * (c.floats ? p.cout : p.cwo) / 2500.0;
+    c.in = qf ? 128.0 * p.n * p.h * p.w * p.cw / 2500.0 : 0.0;
+    c.cw = p.cw;
+    return c;
+}
+
+// A workgroup's region, as the schedules other than the streaming one load it:
+// words and loads per thread.
+struct RegionCost {
+    double words, loads;
+};
+
+RegionCost region_cost(int64_t locations, int cw, bool qf) {
+    const int vec = !qf && cw % 4 == 0 ? 4 : 1;
+    return RegionCost{(double)locations * cw / lce::kMfmaThreads,
+                      std::ceil((double)locations * (cw / vec) / lce::kMfmaThreads)};
+}
+
+double fs_cycles(const FsPlan &fp, const LayerCost &c, int64_t cus, int blocks32, bool qf) {
+    const int64_t wgs = fp.groups * ((blocks32 + 4 / fp.shape.s - 1) / (4 / fp.shape.s));
+    const double w = (double)((wgs + cus - 1) / cus), ks = fp.shape.ks, s = fp.shape.s > 1;
+    const double nb = w * ((fp.pixels + 31) / 32);
+    const RegionCost r = region_cost((int64_t)fp.tile_rows * fp.width, c.cw, qf);
+    if (qf)
+        return 5800.0 + 69.0 * ks + w * (590.0 * std::max(0.0, std::ceil(r.loads / 2) - 1) +
+               1890.0 * r.words) + nb * (45.0 * ks + 13.0 + 510.0 * s + 460.0 * c.floats) +
+               530.0 * wgs / cus + 0.51 * c.out + 0.15 * c.in;
+    return 5200.0 + 220.0 * s + 87.0 * ks + 520.0 * r.loads +
+           nb * (49.0 * ks + 64.0 + 420.0 * s + 490.0 * c.floats) + 680.0 * wgs / cus + 0.43 * c.out;
+}
+
+// (a workgroup is alone on its CU where its LDS leaves no room for another)
+double ks_cycles(const KsPlan &kp, const LayerCost &c, int pw, int64_t cus, int64_t ksteps,
+                 bool qf) {
+    const double q = (double)((ksteps + 3) / 4), blk = kp.mbw * kp.nblk, products = 32.0 * blk * q;
+    const double more = (double)((kp.wgs + cus - 1) / cus) - 1, fl = c.floats * blk;
+    const int64_t fit = device_max_lds() / std::max<int64_t>(1, (int64_t)kp.lds);
+    const double alone = fit < 2, two = fit == 2;
+    const int64_t locations = (int64_t)kp.tile_rows * pw;
+    const RegionCost r = region_cost(locations, c.cw, qf);
+    if (qf)
+        return 7100.0 + 0.76 * products + 9.0 * q +
+               420.0 * std::max(0.0, std::ceil(r.loads / 2) - 1) + 1560.0 * r.words + 764.0 * blk +
+               320.0 * fl + 0.33 * c.out + 0.18 * c.in +
+               0.08 * 128.0 * kp.wgs * locations * c.cw / 2500.0 +
+               more * (1580.0 * r.words + 216.0 * blk + 102.0 * fl +
+                       alone * (8340.0 + 0.68 * products) + 1660.0 * two);
+    return 5910.0 + 0.73 * products + 120.0 * q + 286.0 * r.loads +
+           554.0 * std::ceil(r.loads / 4) + 699.0 * blk + 404.0 * fl + 0.32 * c.out +
+           more * (576.0 + 1.23 * products + 121.0 * r.loads + 84.0 * fl +
+                   alone * (7530.0 + 0.34 * products + 293.0 * r.loads) + 2090.0 * two +
+                   1065.0 * (kp.mbw == 4 && kp.nblk == 1));
+}
+
+// (a workgroup waits for each of its K stages behind a barrier)
+double px_cycles(const PxPlan &b, const LayerCost &c, int pw, int cwe, int cc, int64_t cus,
+                 int64_t ksteps) {
+    const double blk = b.mb * b.nblk, products = 32.0 * blk * ksteps, stages = 2.0 * ksteps / cc;
+    const double more = (double)((b.wgs + cus - 1) / cus) - 1;
+    const int64_t fit = device_max_lds() / std::max<int64_t>(1, (int64_t)(b.lds + b.lds_static));
+    const double alone = fit < 2, two = fit >= 2;
+    const int64_t locations = (int64_t)b.tile_rows * pw;
+    const RegionCost r = region_cost(locations, c.cw, false);
+    const double widened = std::ceil((double)locations / lce::kMfmaThreads) * cwe;
+    return 6140.0 + 0.49 * products + 408.0 * stages + 460.0 * r.loads + 142.0 * widened +
+           263.0 * blk + 637.0 * c.floats * blk + 0.39 * c.out +
+           more * (1.37 * products + 109.0 * r.words + 62.0 * stages + 645.0 * blk +
+                   alone * (4890.0 + 0.15 * products + 243.0 * stages + 423.0 * r.loads) +
+                   233.0 * two);
+}
+
+// (workgroups that share a CU overlap, and take turns beyond those that fit it;
+// a wave's loads of the region cost alike however many of its lanes are in
+// use.  Filters as they are stored: a workgroup's loads of one K step touch some
+// 256 cache lines, and an odd word count takes a division and a mask a step.)
+double stream_cycles(const StreamPlan &s, const LayerCost &c, int64_t cus, int64_t ksteps, bool qf,
+                     bool ohwi) {
+    const double blk = s.mb * s.nb, products = 32.0 * blk * ksteps, odd = c.cw % 2;
+    const int64_t n = (s.tiles * s.groups + cus - 1) / cus;
+    const double words = (double)s.tile_rows * s.width * c.cw / lce::kMfmaThreads;
+    const int vec = qf ? 1 : c.cw % 4 == 0 ? 4 : c.cw % 2 == 0 ? 2 : 1;
+    const int64_t elems = (int64_t)s.width * (c.cw / vec), segs = (elems + 63) / 64;
+    const int64_t units = !qf && elems <= 32 ? (s.tile_rows + 1) / 2 : s.tile_rows * segs;
+    const int64_t u = (units + 3) / 4;                    // region loads of a wave
+    double price = 7870.0 + (blk > 4 ? 2020.0 : 0.0) + 0.96 * products + 37.0 * ksteps +
+                   (127.0 * c.floats + 115.0 * c.edge) * blk + 0.52 * c.out +
+                   (qf ? 1310.0 : 928.0) * u;
+    if (qf)
+        price += 0.2 * c.in + 0.13 * 128.0 * s.tiles * s.groups * s.tile_rows * s.width * c.cw / 2500.0;
+    if (ohwi) price += (272.0 + 305.0 * odd) * ksteps;
+    if (s.per_cu > 1) {
+        const double seq = (double)((n + s.per_cu - 1) / s.per_cu) - 1;
+        const int64_t reg_u = qf ? u : lce::stream_reg_u(vec);
+        const double waits = (double)(std::max<int64_t>(0, u - reg_u) + reg_u - 1) / reg_u;
+        price += (n - 1) * (594.0 + 0.91 * products + (qf ? 510.0 * words : 199.0 * u) + 105.0 * blk) +
+                 seq * ((qf ? 861.0 : 396.0) * u + 225.0 * blk + (qf ? 0.0 : 1628.0 * std::floor(waits)));
+        if (ohwi) price += ((n - 1) * (47.0 + 30.0 * odd) + seq * 106.0) * ksteps;
+    } else {
+        price += (n - 1) * (2516.0 + 1.43 * products + (qf ? 1586.0 : 1117.0) * u);
+        if (ohwi) price += (n - 1) * (252.0 + 100.0 * odd) * ksteps;
+    }
+    return price;
+}
+
+// The generic XOR kernel's price on the same scale: a row's words, which
+// arrive one after another; rounds of workgroups of 64 pixels and 32 filters;
+// xor and popcount instructions (5 cycles each on their SIMD); and the output,
+// 4-byte stores of 64 lanes to 64 cache lines where 16-byte ones do not serve.
+double xor_cycles(const lce_bconv2d_desc &d, int64_t m, int64_t kwords, bool padz, bool wide,
+                  int64_t cus) {
+    const bool bits = d.out_type == LCE_OUT_BITPACKED;
+    const int64_t groups = bits ? packed_words(d.c_out) : (d.c_out + 31) / 32;
+    const double wgs = (double)((m + 63) / 64) * groups, per = wgs / cus;
+    const double xors = (double)m * d.c_out * kwords * 2 / 64 * 5 / (4 * cus);
+    const double out = 4.0 * m * (bits ? packed_words(d.c_out) : d.c_out) / 2500.0;
+    return 6060.0 + 207.0 * kwords + 858.0 * std::ceil(per) + 0.73 * xors + 1.74 * out +
+           per * (474.0 * bits + (wide ? 0.0 : 2600.0) + 233.0 * padz) + 750.0 * padz;
 }
 
 // Whether a tuning key asks for a tile, an instance or a grid of the other
@@ -1038,6 +1187,7 @@ lce::MfmaGeom stream_geometry(const lce::MfmaGeom &g) {
 
 void launch_stream_plan(const lce::MfmaGeom &geom, const lce_bconv2d_desc &d, const StreamPlan &s,
                         int64_t cus, int64_t ksteps, bool qf, bool ohwi, hipStream_t stream) {
+    g_last_schedule = ohwi ? "streaming-stored" : "streaming";
     lce::StreamParams p{};
     static_cast<lce::MfmaGeom &>(p) = geom;
     p.tiles = (int)s.tiles;
@@ -1120,7 +1270,7 @@ bool launch_generic_on_mfma(const lce_bconv2d_desc &d, const Geometry &g, const 
                        aligned(out, 16));
     const double price = 4000.0 + 1.6 * xors + std::max(0.0, 200.0 * kwords - 0.8 * xors) +
                          (wide ? 0.0 : 500.0 * (double)m * d.c_out / 64 / (4 * cus));
-    if (price < 7000.0) return false;                    // (below any streaming plan's)
+    if (price < 7000.0) return false;      // (a call so small that planning is not worth it)
     lce::MfmaParams p;
     if (mfma_params(d, g, x_packed, false, nullptr, multiplier, bias, thresholds, flip, out, &p) !=
         LCE_OK)
@@ -1129,6 +1279,9 @@ bool launch_generic_on_mfma(const lce_bconv2d_desc &d, const Geometry &g, const 
     const lce::MfmaGeom sg = stream_geometry(p);
     const StreamPlan sp = plan_stream(sg, cus, ksteps, p.coutp / 32, false, true);
     if (!sp.mb || sp.cost >= price) return false;
+    if (stream_cycles(sp, layer_cost(p, d.out_type, false), cus, ksteps, false, true) >=
+        xor_cycles(d, m, kwords, zero_padded(d, g), wide, cus))
+        return false;
     launch_stream_plan(sg, d, sp, cus, ksteps, false, true, stream);
     return true;
 }
@@ -1229,8 +1382,10 @@ lce_status lce_bconv2d(const lce_bconv2d_desc *desc, const int32_t *x_packed,
                                stream))
         return check_launch("lce_bconv2d launch");
     if (has_static(p.cw, p.kh, p.kw) && input_fits_buffer(p)) {
+        g_last_schedule = "xor";
         choose_schedule(p, filters);
     } else {
+        g_last_schedule = "xor-generic";
         p.nb = 1; p.ks = 1; p.fwg = lce::kWaves * lce::kRN; p.ksplit = p.kwords;
     }
     p.div_fwg = lce::make_fastdiv((uint32_t)p.fwg);
@@ -1316,6 +1471,7 @@ lce_status lce_quantize_bconv2d(const lce_bconv2d_desc *desc, const float *x,
     p.band_pack = (int32_t)first_area;
     dim3 grid((unsigned)((p.m + lce::kPix - 1) / lce::kPix),
               (unsigned)((filters + p.fwg - 1) / p.fwg));
+    g_last_schedule = "xor-quantize";
     lce::launch_bconv2d_quant(p, d.out_type, grid, (size_t)lds, stream);
     return check_launch("lce_quantize_bconv2d launch");
 }
@@ -1590,22 +1746,40 @@ lce_status lce_bconv2d_mfma(const lce_bconv2d_desc *desc, const int32_t *x_packe
                     "(padded width %d, %d rows)", pp.lds + pp.lds_static, device_max_lds(), p.pw,
                     pp.tile_rows);
 
-    // Streaming: where its price is below that of the schedule it replaces.
-    enum { FS, KS, PX } other = fp.shape.ks ? FS : ks_takes ? KS : PX;
+    // The standing schedule, and what the counts and the prices put before it
+    // (not where a tuning key asks for something of the others).
+    enum Schedule { FS, KS, PX, STREAM };
+    const Schedule standing = fp.shape.ks ? FS : ks_takes ? KS : PX;
+    Schedule other = standing;
+    double count = 0.0;
+    if (sched == 0 || sched == 4)
+        count = other == FS ? fs_count(fp) : other == KS ? ks_count(kp, cus, ksteps)
+                                                         : px_count(pp, cus, ksteps);
     if (sched == 0 && other != FS && kp.mbw && pp.fits &&
-        !tuning(LCE_TUNE_MFMA_TILE_M) && !tuning(LCE_TUNE_MFMA_TILE_N))
-        other = ks_cycles(kp, cus, ksteps) <= px_cycles(pp, cus, ksteps) ? KS : PX;
-    // (not where a tuning key asks for something of the others)
+        !tuning(LCE_TUNE_MFMA_TILE_M) && !tuning(LCE_TUNE_MFMA_TILE_N)) {
+        const double ks = ks_count(kp, cus, ksteps), px = px_count(pp, cus, ksteps);
+        other = ks <= px ? KS : PX;
+        count = std::min(ks, px);
+    }
+    const lce::MfmaGeom sg = stream_geometry(p);
+    StreamPlan sp;
     if (sched == 4 || (sched == 0 && !other_keys())) {
-        const lce::MfmaGeom sg = stream_geometry(p);
-        const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32, false, false);
-        const double price = other == FS   ? fs_cycles(fp)
-                             : other == KS ? ks_cycles(kp, cus, ksteps)
-                                           : px_cycles(pp, cus, ksteps);
-        if (sp.mb && (sched == 4 || sp.cost < price)) {
-            launch_stream_plan(sg, d, sp, cus, ksteps, false, false, stream);
-            return check_launch("lce_bconv2d_mfma launch");
-        }
+        sp = plan_stream(sg, cus, ksteps, blocks32, false, false);
+        if (sp.mb && (sched == 4 || sp.cost < count)) other = STREAM;
+    }
+    if (sched == 0 && other != standing) {
+        const LayerCost lc = layer_cost(p, d.out_type, false);
+        auto cycles = [&](Schedule s) {
+            return s == FS   ? fs_cycles(fp, lc, cus, blocks32, false)
+                   : s == KS ? ks_cycles(kp, lc, p.pw, cus, ksteps, false)
+                   : s == PX ? px_cycles(pp, lc, p.pw, p.cwe, cc, cus, ksteps)
+                             : stream_cycles(sp, lc, cus, ksteps, false, false);
+        };
+        if (cycles(other) >= cycles(standing)) other = standing;
+    }
+    if (other == STREAM) {
+        launch_stream_plan(sg, d, sp, cus, ksteps, false, false, stream);
+        return check_launch("lce_bconv2d_mfma launch");
     }
     if (other == FS)
         launch_fs_plan(p, d, fp, cus, blocks32, ksteps, false, stream);
@@ -1668,8 +1842,8 @@ lce_status lce_quantize_bconv2d_mfma(const lce_bconv2d_desc *desc, const float *
         const KsPlan kp = ks_k ? plan_mfma_ks(p, cus, blocks32) : KsPlan{};
         const FsPlan fp = fs_k && (ksteps <= 36 || sched == 1 || !kp.mbw || kp.wgs < cus)
                               ? plan_mfma_fs(p, cus, blocks32, (int)ksteps) : FsPlan{};
-        // the streaming schedule where one of the two takes the layer and its
-        // price is lower, the float regions' included
+        // the streaming schedule where one of the two takes the layer and the
+        // counts, the float regions' included, and the prices put it first
         if (sched == 4 || (sched == 0 && !other_keys() && (fp.shape.ks || kp.mbw))) {
             const lce::MfmaGeom sg = stream_geometry(p);
             const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32, true, false);
@@ -1682,10 +1856,17 @@ lce_status lce_quantize_bconv2d_mfma(const lce_bconv2d_desc *desc, const float *
                 return 800.0 * std::min(w, 2.0) + 3500.0 * std::max(w - 2.0, 0.0);
             };
             const double price =
-                fp.shape.ks ? fs_cycles(fp) + fp.wpc * stage(fp.tile_rows, fp.width)
-                            : ks_cycles(kp, cus, ksteps) +
+                fp.shape.ks ? fs_count(fp) + fp.wpc * stage(fp.tile_rows, fp.width)
+                            : ks_count(kp, cus, ksteps) +
                                   (double)((kp.wgs + cus - 1) / cus) * stage(kp.tile_rows, p.pw);
-            if (sp.mb && (sched == 4 || sp.cost < price)) {
+            const LayerCost lc = layer_cost(p, d.out_type, true);
+            auto standing = [&] {
+                return fp.shape.ks ? fs_cycles(fp, lc, cus, blocks32, true)
+                                   : ks_cycles(kp, lc, p.pw, cus, ksteps, true);
+            };
+            if (sp.mb && (sched == 4 || (sp.cost < price &&
+                                         stream_cycles(sp, lc, cus, ksteps, true, false) <
+                                             standing()))) {
                 launch_stream_plan(sg, d, sp, cus, ksteps, true, false, stream);
                 return check_launch("lce_quantize_bconv2d_mfma launch");
             }
@@ -1712,5 +1893,7 @@ int32_t lce_get_tuning(int32_t key) {
 }
 
 const char *lce_last_error(void) { return g_last_error.c_str(); }
+
+const char *lce_last_schedule(void) { return g_last_schedule; }
 
 }  // extern "C"
