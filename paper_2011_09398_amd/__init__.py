@@ -536,8 +536,9 @@ def quantize_bconv2d_mfma(x, w_fp4, c_out: int, kernel, *, stride=1, padding: st
     """LceQuantize + LceBConv2d on the matrix cores in one launch: x float32
     [N,H,W,C_in] (C_in a multiple of 32, 16-byte aligned), w_fp4 from
     mfma_weights().  The result equals bconv2d_mfma(bitpack(x), ...).  Shapes
-    the filter-stationary schedule does not take raise LceError with status
-    LCE_EUNSUPPORTED (nothing is launched); run bitpack and bconv2d_mfma."""
+    that neither the filter-stationary nor the K-split schedule takes raise
+    LceError with status LCE_EUNSUPPORTED (nothing is launched); run bitpack and
+    bconv2d_mfma."""
     return _mfma_conv(lib().lce_quantize_bconv2d_mfma, x, True, w_fp4, x.shape[-1], c_out,
                       kernel, stride, padding, pad_value, clamp, out_type, multiplier, bias,
                       thresholds, flip, out)

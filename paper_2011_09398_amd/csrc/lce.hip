@@ -1844,7 +1844,7 @@ lce_status lce_quantize_bconv2d_mfma(const lce_bconv2d_desc *desc, const float *
                               ? plan_mfma_fs(p, cus, blocks32, (int)ksteps) : FsPlan{};
         // the streaming schedule where one of the two takes the layer and the
         // counts, the float regions' included, and the prices put it first
-        if (sched == 4 || (sched == 0 && !other_keys() && (fp.shape.ks || kp.mbw))) {
+        if ((fp.shape.ks || kp.mbw) && (sched == 4 || (sched == 0 && !other_keys()))) {
             const lce::MfmaGeom sg = stream_geometry(p);
             const StreamPlan sp = plan_stream(sg, cus, ksteps, blocks32, true, false);
             // their float regions: two words per thread in one round of loads,

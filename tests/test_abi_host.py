@@ -199,6 +199,11 @@ def test_quantize_bconv2d_mfma_schedule_key_refusals():
         lce.set_tuning(mfma_schedule="fs")
         assert call_quant_mfma(desc(c_in=160, c_out=32)) == lce.LCE_EUNSUPPORTED
         assert "27 K steps" in lce.last_error()
+        # streaming: only for the shapes that the others cover, also where its
+        # column tiles would take the width (regions of 3 rows of 30,002 columns)
+        lce.set_tuning(mfma_schedule="stream")
+        assert call_quant_mfma(desc(n=1, h=3, w=30000, c_in=32, c_out=32)) == lce.LCE_EUNSUPPORTED
+        assert "9 K steps" in lce.last_error()
     finally:
         lce.set_tuning(mfma_schedule=0)
 
