@@ -799,12 +799,19 @@ struct KsPlan {
     size_t lds = 0;
 };
 
+// The tile keys, for the K split and the pixel split: with the streaming
+// schedule forced they are its own, and the others plan as without them (a shape
+// is covered or not whatever its tile).
+int tile_key(lce_tuning_key key) {
+    return tuning(LCE_TUNE_MFMA_SCHEDULE) == 4 ? 0 : tuning(key);
+}
+
 KsPlan plan_mfma_ks(const lce::MfmaParams &p, int64_t cus, int blocks32) {
     const int nmax = blocks32 >= 4 ? 4 : blocks32 >= 2 ? 2 : 1;
     static const int kTiles[][2] = {{4, 2}, {2, 4}, {2, 2}, {4, 1}, {1, 4},
                                     {2, 1}, {1, 2}, {1, 1}};
     KsPlan best;
-    const int env_mb = tuning(LCE_TUNE_MFMA_TILE_M), env_nb = tuning(LCE_TUNE_MFMA_TILE_N);
+    const int env_mb = tile_key(LCE_TUNE_MFMA_TILE_M), env_nb = tile_key(LCE_TUNE_MFMA_TILE_N);
     for (const auto &o : kTiles) {
         if (o[1] > nmax) continue;
         if (env_mb && o[0] != env_mb) continue;
@@ -974,8 +981,8 @@ PxPlan plan_mfma_pixel(const lce::MfmaParams &p, int64_t cus, int blocks32, int 
         if (wgs >= cus) { b.mb = o[0]; b.nblk = o[1]; break; }
         if (wgs > best_wgs) { best_wgs = wgs; b.mb = o[0]; b.nblk = o[1]; }
     }
-    if (const int t = tuning(LCE_TUNE_MFMA_TILE_N)) b.nblk = t;
-    if (const int t = tuning(LCE_TUNE_MFMA_TILE_M)) b.mb = t;
+    if (const int t = tile_key(LCE_TUNE_MFMA_TILE_N)) b.nblk = t;
+    if (const int t = tile_key(LCE_TUNE_MFMA_TILE_M)) b.mb = t;
     if (b.nblk != 1 && b.nblk != 2 && b.nblk != 4) b.nblk = 4;
     if (b.mb != 1 && b.mb != 2) b.mb = 2;
     const int bm = 128 * b.mb;
