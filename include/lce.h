@@ -363,7 +363,10 @@ typedef enum {
                                      blocks                                             */
     LCE_TUNE_MFMA_FS_WINDOW = 10, /* -1: filter-stationary workgroups stage whole padded
                                      rows, also where a share's window of columns would do */
-    LCE_TUNE_COUNT = 11
+    LCE_TUNE_XOR_STREAM = 11,     /* lce_bconv2d, filter shapes without a specialized XOR
+                                     instance: 1 the streaming schedule (where a tile
+                                     fits; tile and grid keys as above), -1 the XOR kernel */
+    LCE_TUNE_COUNT = 12
 } lce_tuning_key;
 
 /* Set override `key` to `value` (0 = automatic).

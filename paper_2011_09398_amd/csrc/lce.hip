@@ -876,6 +876,10 @@ double fs_count(const FsPlan &fp) {
 StreamPlan plan_stream(const lce::MfmaGeom &p, int64_t cus, int64_t ksteps, int blocks32,
                        bool qf, bool ohwi) {
     StreamPlan best;
+    // (exact: a threshold within +-(K + 1), the padding channels' sum and the dot
+    // stay below 2^24 together.  The step table's LDS ends at 2.6 M channels
+    // anyway.)
+    if (64 * ksteps >= 1 << 22) return best;
     const int force_mb = tuning(LCE_TUNE_MFMA_TILE_M), force_bn = tuning(LCE_TUNE_MFMA_TILE_N);
     // {mb, nb, wf}
     static const int kTiles[][3] = {{2, 2, 1}, {2, 2, 2}, {2, 2, 4}, {4, 2, 1}, {4, 2, 2},
@@ -1241,15 +1245,15 @@ void launch_stream_plan(const lce::MfmaGeom &geom, const lce_bconv2d_desc &d, co
 }
 
 // lce_bconv2d, shapes without a specialized XOR/POPCOUNT instance: the
-// streaming matrix-core schedule on the filters as they are stored, where its
-// price is below the generic XOR kernel's (the same integers: K < 2^22 keeps
-// the fp32 accumulation exact).  The generic kernel's price, in cycles: its xor
-// and popcount instructions (5 each on their SIMD) and 0.6 times as long again
-// for staging every im2col row for each 32 filters (3x3/2 200->136 over 45x61
-// batch 64: 100K, 98K measured); a row's words, which arrive one after another,
-// where other waves' instructions do not cover them (5x5x480 8x8 batch 7: 83K,
-// 86K); and 4-byte stores of 64 lanes to 64 cache lines where the 16-byte ones
-// do not serve (1x1 38->228 over 80K pixels: 148K, 185K).
+// streaming matrix-core schedule on the filters as they are stored (the same
+// integers), where its count is below the generic XOR kernel's and the prices
+// agree.  The generic kernel's count, in cycles: its xor and popcount
+// instructions (5 each on their SIMD) and 0.6 times as long again for staging
+// every im2col row for each 32 filters (3x3/2 200->136 over 45x61 batch 64:
+// 100K, 98K measured); a row's words, which arrive one after another, where
+// other waves' instructions do not cover them (5x5x480 8x8 batch 7: 83K, 86K);
+// and 4-byte stores of 64 lanes to 64 cache lines where the 16-byte ones do not
+// serve (1x1 38->228 over 80K pixels: 148K, 185K).
 // us XOR -> here: 1x1 256->512 28x28 batch 256 158 -> 35, 1x1 367->222 19x76
 // batch 143 228 -> 40, 7x7/2 45->223 74x41 batch 74 126 -> 47, 5x5 416->224
 // 9x40 batch 89 251 -> 101, 3x3/2 200->136 45x61 batch 64 49 -> 31.
@@ -1260,15 +1264,15 @@ bool launch_generic_on_mfma(const lce_bconv2d_desc &d, const Geometry &g, const 
                             const float *thresholds, const int32_t *flip, void *out,
                             hipStream_t stream) {
     const int cw = packed_words(d.c_in);
-    if (has_static(cw, d.kh, d.kw) || tuning(LCE_TUNE_XOR_NB) || tuning(LCE_TUNE_XOR_KS) ||
-        other_keys())
+    const int force = tuning(LCE_TUNE_XOR_STREAM);
+    if (has_static(cw, d.kh, d.kw) || force < 0) return false;
+    if (!force && (tuning(LCE_TUNE_XOR_NB) || tuning(LCE_TUNE_XOR_KS) || other_keys()))
         return false;
     int cc, cwe;
     mfma_chunk(cw, &cc, &cwe);
     const int64_t ksteps = (int64_t)d.kh * d.kw * (cwe / 2);
     const int64_t m = (int64_t)d.n * g.oh * g.ow, kwords = (int64_t)d.kh * d.kw * cw;
-    if (64 * ksteps >= 1 << 22 || m > INT32_MAX - lce::kMfmaPixMax ||
-        (int64_t)d.c_out * kwords * 4 >= int64_t(1) << 31)
+    if (m > INT32_MAX - lce::kMfmaPixMax || (int64_t)d.c_out * kwords * 4 >= int64_t(1) << 31)
         return false;
     const int64_t cus = device_simds() / 4;
     const double xors = (double)m * d.c_out * kwords * 2 / 64 * 5 / (4 * cus);
@@ -1277,7 +1281,7 @@ bool launch_generic_on_mfma(const lce_bconv2d_desc &d, const Geometry &g, const 
                        aligned(out, 16));
     const double price = 4000.0 + 1.6 * xors + std::max(0.0, 200.0 * kwords - 0.8 * xors) +
                          (wide ? 0.0 : 500.0 * (double)m * d.c_out / 64 / (4 * cus));
-    if (price < 7000.0) return false;      // (a call so small that planning is not worth it)
+    if (!force && price < 7000.0) return false;   // (a call so small that planning is not worth it)
     lce::MfmaParams p;
     if (mfma_params(d, g, x_packed, false, nullptr, multiplier, bias, thresholds, flip, out, &p) !=
         LCE_OK)
@@ -1285,8 +1289,8 @@ bool launch_generic_on_mfma(const lce_bconv2d_desc &d, const Geometry &g, const 
     p.wpk = reinterpret_cast<const uint32_t *>(w_packed);
     const lce::MfmaGeom sg = stream_geometry(p);
     const StreamPlan sp = plan_stream(sg, cus, ksteps, p.coutp / 32, false, true);
-    if (!sp.mb || sp.cost >= price) return false;
-    if (stream_cycles(sp, layer_cost(p, d.out_type, false), cus, ksteps, false, true) >=
+    if (!sp.mb || (!force && sp.cost >= price)) return false;
+    if (!force && stream_cycles(sp, layer_cost(p, d.out_type, false), cus, ksteps, false, true) >=
         xor_cycles(d, m, kwords, zero_padded(d, g), wide, cus))
         return false;
     launch_stream_plan(sg, d, sp, cus, ksteps, false, true, stream);

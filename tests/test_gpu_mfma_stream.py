@@ -124,20 +124,23 @@ def test_stream_thresholds_and_flip(stream):
 
 
 def test_stream_is_chosen_and_agrees(stream):
-    """Layers that the library's own choice runs on this schedule (a share of
-    pixels too large for the filter-stationary region; short and long K):
-    equal to the K split and the pixel split, bit for bit."""
+    """Layers that the library's own choice runs on this schedule (large batches;
+    short and long K), and one of long shares that it leaves to another: equal to
+    the K split and the pixel split, bit for bit."""
     import torch
-    for n, h, c_in, c_out, k in ((256, 14, 256, 64, 3), (300, 28, 64, 64, 1),
-                                 (150, 13, 96, 128, 5)):
+    for n, h, c_in, c_out, k, chosen in ((256, 14, 256, 256, 3, True), (300, 28, 64, 256, 1, True),
+                                         (150, 13, 96, 128, 5, True), (20, 14, 256, 64, 3, False)):
         g = torch.Generator("cuda").manual_seed(5)
         xp = stream.bitpack(torch.randn(n, h, h, c_in, device="cuda", generator=g))
         wp = stream.bitpack(torch.randn(c_out, k, k, c_in, device="cuda", generator=g))
         wf = stream.mfma_weights(wp, c_in)
         outs = []
-        for sched in ("auto", "stream", "ksplit", "pixel"):
+        for sched, name in (("auto", "streaming" if chosen else "filter-stationary"),
+                            ("stream", "streaming"), ("ksplit", "k-split"),
+                            ("pixel", "pixel-split")):
             stream.set_tuning(mfma_schedule=sched)
             outs.append(stream.bconv2d_mfma(xp, wf, c_in, c_out, k, out_type="int32"))
+            assert stream.last_schedule() == name, (n, h, c_in, c_out, k, sched)
         for o in outs[1:]:
             assert torch.equal(outs[0], o)
 
