@@ -671,6 +671,10 @@ def measured_traffic(layer_name, kind):
     return rec["per_launch_bytes"].get(layer_name)
 
 
+# Sections of the result that are printed on stderr (the sweep alone is 10 KB).
+DETAILS = ("stack16", "cpu_batch1", "zero_padding", "conv_sweep")
+
+
 def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
@@ -805,6 +809,10 @@ def main():
             "binary_tops": round(probe, 1), "spec_binary_tops": round(PEAK_BINARY_TOPS, 1)},
         "device": torch.cuda.get_device_name(0),
     }
+    # The long sections go to stderr, one line each, so that the line on stdout
+    # stays short enough to be kept whole by what records its last few KB.
+    for key in DETAILS:
+        log(f"details {json.dumps({key: line.pop(key)})}")
     print(json.dumps(line), flush=True)
 
 
