@@ -131,7 +131,7 @@ lce_status lce_bitpack(const float *x, int32_t *out, int64_t rows, int32_t chann
  *   out        see lce_out_type; shape from lce_bconv2d_out_shape
  * Dilation and groups are not part of the operator (always 1).
  * Filter shapes without a specialized XOR/POPCOUNT instance run on the matrix
- * cores (below; the same integers) where that is the faster way.
+ * cores (below; the same integers) where that is priced as the faster way.
  * All pointers must be 4-byte aligned.
  * Errors: LCE_EINVAL (null desc or required pointer, bad field, no output,
  *         c_out > 2^20, a tensor of 2^31 or more words/elements; with zero
@@ -233,9 +233,10 @@ lce_status lce_bconv2d_mfma_weights_size(const lce_bconv2d_desc *desc, int64_t *
  * -1.0 = 0xA), channel 32j + c in 32-bit word c % 4, nibble c / 4.  Channels
  * past C_in and filters past C_out widen to 0.0.  Then, from byte
  * 16*KH*KW*Cw'*C_out' on, the same elements as packed 32-bit words (bit 1 =
- * -1; channels past C_in, words past Cw and filters past C_out 0): where
- * C_in = 32*Cw', the filter-stationary schedule loads these and widens
- * them itself.  Run once per filter tensor.
+ * -1; channels past C_in, words past Cw and filters past C_out 0): the
+ * streaming schedule reads these alone, for every C_in, and the
+ * filter-stationary one where C_in = 32*Cw', and they widen them themselves.
+ * Run once per filter tensor.
  * Errors: LCE_EINVAL, LCE_EALIGN, LCE_EHIP. */
 lce_status lce_bconv2d_mfma_weights(const lce_bconv2d_desc *desc, const int32_t *w_packed,
                                     void *w_fp4, hipStream_t stream);

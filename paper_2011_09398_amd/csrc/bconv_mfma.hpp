@@ -11,8 +11,8 @@
 // bitpacked in memory; each 1-bit value is widened to a 4-bit +-1.0 only in
 // LDS, right before the matrix cores read it.
 //
-// Instruction: v_mfma_scale_f32_32x32x64_f8f6f4 with both operands fp4 and
-// unit scales (E8M0 127 = 2^0).  Lane l holds row (or column) l % 32 and one
+// Instruction: v_mfma_f32_32x32x64_f8f6f4 with both operands fp4, the form
+// without scales.  Lane l holds row (or column) l % 32 and one
 // block of 32 consecutive k values, l / 32 choosing the block.  A dot product
 // does not depend on the order of k, so a lane's block is simply one packed
 // word (32 channels of one tap) widened to 16 bytes; the filter side is
@@ -81,6 +81,7 @@ struct MfmaGeom {
                                      // from the end of the A tile
     int32_t pad_zero;                // 1: padded locations are 0.0
     int32_t region_vec;              // words per lane per load when staging the region: 4 or 1
+                                     // (streaming also 2, and 0 for a float32 input)
     FastDiv div_ohw, div_ow, div_ph, div_pw;
     FastDiv div_plane;               // tile_rows * pw: region locations
     FastDiv div_cwh, div_kw;         // cwe / 2 (word pairs per tap), kw

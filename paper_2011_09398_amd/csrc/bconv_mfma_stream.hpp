@@ -32,13 +32,15 @@
 // Measured (us; the schedule that took the layer before, and this one):
 // 56x56x64->64 batch 256 44.9 -> 21.5, 14x14x256 batch 256 42 -> 15.8,
 // 7x7x512 batch 256 32.7 -> 16.8, 1x1 28x28x256->512 batch 256 58 -> 30,
-// 5x5 64x64x256 batch 32 (float) 155 -> 85, 3x3 360x640x64 x2 (float) 46 -> 26;
+// 5x5 64x64x256 batch 32 (float) 156 -> 79, 3x3 360x640x64 x2 (float) 48 -> 25;
 // from float32 input 56x56x64->64 batch 256 (212 MB) 65 -> 48, 28x28x128 batch
 // 128 with float output (103 MB) 28.5 -> 23, 14x14x256 batch 256 90 -> 27.
 // What bounds it: 56x56x64 spends 13.5K of 37K cycles per wave in the
-// products, the rest in staging, output and waiting; with long K (5x5x256) it
-// is the matrix pipe at the clock that random +-1 data leave it (about 8
-// PFLOP/s in a loop of products alone; here 6.2).
+// products (the matrix pipes are busy 34% of the time), the rest in staging,
+// output and waiting, where the scalar registers that the compiler spills (76
+// there) are reloaded; with long K (5x5x256, busy 71%) it is the matrix pipe at
+// the clock that random +-1 data leave it (about 8 PFLOP/s in a loop of products
+// alone; here 5.4 with its 134 MB of output).
 #pragma once
 
 #include "bconv_mfma.hpp"
